@@ -76,7 +76,7 @@ struct nxs_context {
   // workspace
   DevBuf views, counters, partials, status;
   DevBuf depth_key, dsort_a, dsort_b, slot_a, slot_b, trect, nt_sorted, rect_sorted, prec;
-  DevBuf scan_local, block_sums, counts;
+  DevBuf scan_local, block_sums, counts, cells, segs;
   DevBuf inst_tile, inst_tile_alt, inst_val, inst_val_alt;
   DevBuf ranges, pstate, gslot, order;
   int n_cu = 256;
@@ -117,6 +117,8 @@ struct nxs_context {
   int32_t last_n = 0, last_views = 0;
   uint32_t* last_inst_tile = nullptr;
   uint32_t* last_inst_val = nullptr;
+  // the tile lists lie cell by cell (two-level binning; no tile keys are kept)
+  bool last_by_cell = false;
   const nxs_fwd_state* last_state = nullptr;   // holds last_inst_val, if any
   // instances of the context's last known render: a deferred render's tile
   // sort and ranges are launched for about this many (and loop beyond it)
@@ -227,7 +229,8 @@ void free_workspace(nxs_context* ctx, hipStream_t s) {
                     &ctx->slot_b,     &ctx->trect,     &ctx->nt_sorted,     &ctx->rect_sorted,
                     &ctx->prec,       &ctx->scan_local, &ctx->block_sums,   &ctx->counts,
                     &ctx->inst_tile,  &ctx->inst_tile_alt, &ctx->inst_val,  &ctx->inst_val_alt,
-                    &ctx->ranges,     &ctx->pstate,    &ctx->gslot,         &ctx->order};
+                    &ctx->ranges,     &ctx->pstate,    &ctx->gslot,         &ctx->order,
+                    &ctx->cells,      &ctx->segs};
   for (DevBuf* b : list) drop(ctx, *b, s, true);
   ctx->ws_total = 0;
   ctx->status_clear = false;
@@ -254,11 +257,9 @@ uint64_t instance_capacity(const nxs_context* ctx) {
   return std::min<uint64_t>(c / 4, 0xFFFFFFFEull);
 }
 
-nxs_status grow_instances(nxs_context* ctx, uint64_t m, int64_t S, hipStream_t s) {
+nxs_status grow_instances(nxs_context* ctx, uint64_t m, hipStream_t s) {
   nxs_status st;
-  if ((st = ensure(ctx, ctx->counts, 4 * radix_counts_words(std::max<int64_t>(S, (int64_t)m)),
-                   s)) ||
-      (st = ensure(ctx, ctx->inst_tile, 4 * m, s)) ||
+  if ((st = ensure(ctx, ctx->inst_tile, 4 * m, s)) ||
       (st = ensure(ctx, ctx->inst_tile_alt, 4 * m, s)) ||
       (st = ensure(ctx, ctx->inst_val, 4 * m, s)) ||
       (st = ensure(ctx, ctx->inst_val_alt, 4 * m, s)))
@@ -274,7 +275,7 @@ nxs_status nxs::grow_instance_capacity(nxs_context* ctx, uint64_t need) {
   HIP_TRY(hipSetDevice(ctx->device));
   if (ctx->has_done) HIP_TRY(hipEventSynchronize(ctx->done));
   if (need == 0 || need >= 0xFFFFFFFFull || need <= instance_capacity(ctx)) return NXS_OK;
-  return grow_instances(ctx, need, ctx->last_slots, nullptr);
+  return grow_instances(ctx, need, nullptr);
 }
 
 namespace {
@@ -428,6 +429,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   if (ctx->has_done) HIP_TRY(hipStreamWaitEvent(s, ctx->done, 0));
   ctx->last_inst_tile = ctx->last_inst_val = nullptr;
   ctx->last_state = nullptr;
+  ctx->last_by_cell = false;
   ctx->last_m = 0;
   ctx->last_deferred = false;
   ctx->last_failed = false;
@@ -462,7 +464,15 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     }
   }
   ViewDev* host_views = by_arg ? arg_views.data() : ctx->host_views[ring];
-  int64_t off = 0, pix_off = 0;
+  std::vector<int32_t> grid_xy(2 * (size_t)n_views);
+  for (int v = 0; v < n_views; ++v) {
+    grid_xy[v] = (cams[v].width + tw - 1) / tw;
+    grid_xy[n_views + v] = (cams[v].height + th - 1) / th;
+  }
+  const BinPlan bins = plan_bins(grid_xy.data(), grid_xy.data() + n_views, n_views, g->n);
+  const bool by_cell = bins.n_cells > 0;
+  const int sort_parts = by_cell ? n_views : 1;   // each view's slots on their own
+  int64_t off = 0, pix_off = 0, cell_off = 0;
   for (int v = 0; v < n_views; ++v) {
     const nxs_camera& cm = cams[v];
     ViewDev& d = host_views[v];
@@ -474,10 +484,15 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
       d.campos[k] = (float)-((double)cm.R[k] * cm.t[0] + (double)cm.R[3 + k] * cm.t[1] +
                              (double)cm.R[6 + k] * cm.t[2]);
     d.width = cm.width; d.height = cm.height;
-    d.tiles_x = (cm.width + tw - 1) / tw;
-    d.tiles_y = (cm.height + th - 1) / th;
+    d.tiles_x = grid_xy[v];
+    d.tiles_y = grid_xy[n_views + v];
     d.tile_off = (int32_t)off;
     off += (int64_t)d.tiles_x * d.tiles_y;
+    if (by_cell) {
+      d.cell_off = (int32_t)cell_off;
+      d.cells_x = (d.tiles_x + (1 << bins.sx) - 1) >> bins.sx;
+      cell_off += (int64_t)d.cells_x * ((d.tiles_y + (1 << bins.sy) - 1) >> bins.sy);
+    }
     d.pix_off = pix_off;
     pix_off += (int64_t)cm.width * cm.height;
     d.rgb = out[v].rgb; d.trans = out[v].trans; d.od = out[v].overdraw;
@@ -506,13 +521,20 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   if ((st = ensure(ctx, ctx->depth_key, 4 * S, s)) || (st = ensure(ctx, ctx->dsort_a, 4 * S, s)) ||
       (st = ensure(ctx, ctx->dsort_b, 4 * S, s)) ||
       (st = ensure(ctx, ctx->slot_a, 4 * S, s)) || (st = ensure(ctx, ctx->slot_b, 4 * S, s)) ||
-      (st = ensure(ctx, ctx->trect, 8 * S, s)) || (st = ensure(ctx, ctx->nt_sorted, 4 * S, s)) ||
+      (st = ensure(ctx, ctx->trect, 8 * S, s)) ||
       (st = ensure(ctx, ctx->rect_sorted, 8 * S, s)) ||
-      (st = ensure(ctx, ctx->prec, 48 * S, s)) || (st = ensure(ctx, ctx->scan_local, 4 * S, s)) ||
-      (st = ensure(ctx, ctx->block_sums, 4 * scan_blocks_size(S), s)) ||
-      (st = ensure(ctx, ctx->counts, 4 * radix_counts_words(S), s)) ||
+      (st = ensure(ctx, ctx->prec, 48 * S, s)) ||
+      (st = ensure(ctx, ctx->counts,
+                   4 * std::max(radix_counts_words(S / sort_parts, sort_parts), bin_counts_words(bins)), s)) ||
       (st = ensure(ctx, ctx->ranges, 8 * total_tiles + 4 * kSchedCounters, s)))
     return st;
+  if (by_cell) {
+    if ((st = ensure(ctx, ctx->cells, 4 * bin_cells_words(bins), s))) return st;
+  } else if ((st = ensure(ctx, ctx->nt_sorted, 4 * S, s)) ||
+             (st = ensure(ctx, ctx->scan_local, 4 * S, s)) ||
+             (st = ensure(ctx, ctx->block_sums, 4 * scan_blocks_size(S), s))) {
+    return st;
+  }
   uint64_t icap = 0;   // deferred: the instances this render may use
   if (deferred) {
     if ((st = ensure(ctx, ctx->status, sizeof(DeferredStatus), s))) return st;
@@ -523,7 +545,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     icap = instance_capacity(ctx);
     // (the count of the latest deferred render whose status has landed)
     if (ctx->host_status->last) ctx->m_hint = ctx->host_status->last;
-    if ((st = ensure(ctx, ctx->counts, 4 * radix_counts_words(std::max<int64_t>(S, icap)), s)))
+    if (!by_cell &&
+        (st = ensure(ctx, ctx->counts, 4 * radix_counts_words(std::max<int64_t>(S, icap)), s)))
       return st;
   }
   ProjDev proj{P<uint32_t>(ctx->depth_key), P<uint2>(ctx->trect), P<float4>(ctx->prec)};
@@ -574,34 +597,54 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   }
   HIP_TRY(mark(2));
   // 1. depth sort of the slots (values: the slots 0..S-1)
-  //    (its last pass also lays out the slots' tile counts and rectangles in
-  //    that order, so that the emission reads them coalesced)
+  //    (its last pass also lays out the slots' rectangles in that order, so
+  //    that the binning reads them coalesced)
   //    (launched from the pass the last render's plan needed; checked below,
   //    or on the device for a deferred render)
   auto depth_sort = [&](int first) {
     return radix_sort_planned(P<uint32_t>(ctx->depth_key), nullptr, P<uint32_t>(ctx->dsort_a),
                               P<uint32_t>(ctx->slot_a), P<uint32_t>(ctx->dsort_b),
-                              P<uint32_t>(ctx->slot_b), S, dcount->plan, first,
+                              P<uint32_t>(ctx->slot_b), S / sort_parts, sort_parts,
+                              dcount->plan, first,
                               P<uint32_t>(ctx->counts), proj.trect,
-                              P<uint32_t>(ctx->nt_sorted), P<uint2>(ctx->rect_sorted), s);
+                              by_cell ? nullptr : P<uint32_t>(ctx->nt_sorted),
+                              P<uint2>(ctx->rect_sorted), s);
   };
-  // (tile first: no depth sort; the slots are emitted in their own order)
+  // (tile first: no depth sort; the slots are binned in their own order)
   uint32_t* sorted_slots = nullptr;
   if (!tile_first) {
     const int wd = depth_sort(depth_first);
     sorted_slots = wd ? P<uint32_t>(ctx->slot_b) : P<uint32_t>(ctx->slot_a);
   }
-  const uint32_t* nt_in = tile_first ? nullptr : P<uint32_t>(ctx->nt_sorted);
-  const uint2* rect_in = tile_first ? nullptr : P<uint2>(ctx->rect_sorted);
+  const uint2* rects = tile_first ? proj.trect : P<uint2>(ctx->rect_sorted);
   HIP_TRY(mark(3));
-  // 2. emission (in depth order, or in slot order), into the buffers as they are
-  launch_emit_scan(nt_in, proj.trect, S, P<uint32_t>(ctx->scan_local),
-                   P<uint32_t>(ctx->block_sums), s);
-  const uint32_t cap32 = (uint32_t)instance_capacity(ctx);
-  if (cap32 > 0)
-    launch_emit_write(sorted_slots, rect_in, proj.trect, S, g->n, dviews,
-                      P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums), cap32,
-                      P<uint32_t>(ctx->inst_tile), P<uint32_t>(ctx->inst_val), s);
+  // 2. binning (in depth order, or in slot order): the slots' cells counted and,
+  //    with the buffers as they are, dealt to the cells; or, for very many
+  //    cells, every instance emitted
+  BinBuffers bb{P<uint32_t>(ctx->counts), P<uint32_t>(ctx->cells), nullptr, nullptr, nullptr,
+                nullptr, P<uint2>(ctx->ranges)};
+  auto count_slots = [&]() {
+    if (by_cell)
+      launch_bin_count(bins, bb, rects, dviews, dcount, s);
+    else
+      launch_emit_scan(tile_first ? nullptr : P<uint32_t>(ctx->nt_sorted), proj.trect, S,
+                       P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums), s);
+  };
+  auto write_slots = [&](uint64_t cap) {
+    if (by_cell) {
+      bb.pair_slot = P<uint32_t>(ctx->inst_tile);
+      bb.pair_rect = P<uint16_t>(ctx->inst_tile_alt);
+      launch_bin_scatter(bins, bb, sorted_slots, rects, dviews, cap, dcount, s);
+    } else {
+      launch_emit_write(sorted_slots, tile_first ? nullptr : rects, proj.trect, S, g->n, dviews,
+                        P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums),
+                        (uint32_t)cap, P<uint32_t>(ctx->inst_tile), P<uint32_t>(ctx->inst_val),
+                        s);
+    }
+  };
+  count_slots();
+  const uint64_t cap_now = instance_capacity(ctx);
+  if (cap_now > 0) write_slots(cap_now);
   HIP_TRY(hipGetLastError());
   uint64_t M = 0;          // instances (deferred: their upper bound)
   if (!deferred) {
@@ -615,7 +658,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     ctx->m_hint = M;
     if (!ctx->noalloc) ctx->host_status->last = 0;
     // the depth sort skipped pass 0 but this render's plan needs it: sort and
-    // emit again below (the depth keys are intact)
+    // bin again below (the depth keys are intact)
     const bool pass0 = (ctx->host_counters->plan[0] & kPassActive) != 0;
     const bool resort = !tile_first && S > 0 && depth_first == 1 && pass0;
     if (!ctx->noalloc) ctx->depth_first = pass0 ? 0 : 1;
@@ -626,17 +669,15 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
       return fail(ctx, NXS_ECAPACITY, "%llu tile instances exceed the 32-bit range",
                   (unsigned long long)M);
     // ---- instance buffers (growing them is stream-ordered) -------------------
-    if ((st = grow_instances(ctx, M, S, s))) return st;
+    if ((st = grow_instances(ctx, M, s))) return st;
+    if (!by_cell &&
+        (st = ensure(ctx, ctx->counts, 4 * radix_counts_words(std::max<int64_t>(S, M)), s)))
+      return st;
     if (resort) {
       (void)depth_sort(0);
-      launch_emit_scan(nt_in, proj.trect, S, P<uint32_t>(ctx->scan_local),
-                       P<uint32_t>(ctx->block_sums), s);
+      count_slots();
     }
-    if (resort || M > cap32)   // emit (again) into the grown buffers
-      launch_emit_write(sorted_slots, rect_in, proj.trect, S, g->n, dviews,
-                        P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums),
-                        (uint32_t)M, P<uint32_t>(ctx->inst_tile), P<uint32_t>(ctx->inst_val),
-                        s);
+    if (resort || M > cap_now) write_slots(M);   // (again) into the grown buffers
   } else {
     M = icap;
     ctx->last_m = -1;
@@ -650,11 +691,22 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
                               : ctx->m_hint;
   const int64_t m_plan =
       deferred ? (int64_t)std::min<uint64_t>(M, expect + expect / 4 + 4096) : (int64_t)M;
-  uint32_t* inst_tile = P<uint32_t>(ctx->inst_tile);
+  uint32_t* inst_tile = by_cell ? nullptr : P<uint32_t>(ctx->inst_tile);
   uint32_t* inst_val = P<uint32_t>(ctx->inst_val);
   bool list_alt = false;
   HIP_TRY(mark(4));
-  if (M > 0) {
+  if (by_cell && M > 0 && S > 0) {
+    // 3. the cells' lists expanded into the tiles'
+    const size_t seg_bytes = 4 * bin_seg_words(bins, M);
+    bb.segs = P<uint32_t>(ctx->inst_val_alt);
+    if (seg_bytes > ctx->inst_val_alt.cap) {   // (few instances over many cells)
+      if ((st = ensure(ctx, ctx->segs, seg_bytes, s))) return st;
+      bb.segs = P<uint32_t>(ctx->segs);
+    }
+    bb.list = inst_val;
+    launch_bin_tiles(bins, bb, (uint64_t)m_plan, dviews, dcount, s);
+    HIP_TRY(mark(5));
+  } else if (!by_cell && M > 0) {
     // 3. stable sort by global tile
     const int tbits = bit_length((uint64_t)(total_tiles - 1));
     const int wt = radix_sort(inst_tile, inst_val, P<uint32_t>(ctx->inst_tile_alt),
@@ -668,16 +720,16 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     HIP_TRY(mark(5));
     // 4. tile ranges
     launch_ranges(inst_tile, (int64_t)M, P<uint2>(ctx->ranges), s, dn, m_plan);
-    // 4a. tile first: each tile's list (in slot order) by depth, through the
-    //     buffer the tile sort left free
-    if (tile_first)
-      launch_tile_depth_sort(P<uint2>(ctx->ranges), total_tiles, P<uint32_t>(ctx->depth_key),
-                             dcount, inst_val,
-                             list_alt ? P<uint32_t>(ctx->inst_val) : P<uint32_t>(ctx->inst_val_alt),
-                             s);
   } else {
     HIP_TRY(mark(5));
   }
+  // 4a. tile first: each tile's list (in slot order) by depth, through the
+  //     buffer the binning left free
+  if (M > 0 && tile_first)
+    launch_tile_depth_sort(P<uint2>(ctx->ranges), total_tiles, P<uint32_t>(ctx->depth_key),
+                           dcount, inst_val,
+                           list_alt ? P<uint32_t>(ctx->inst_val) : P<uint32_t>(ctx->inst_val_alt),
+                           s);
   // 4b. the tile order of the queue schedules (longest tile lists first)
   // (the composite gathers the records of the sorted slots batch by batch)
   CompositeLaunch cl{sched, tw, th, total_tiles, dviews, n_views, P<uint2>(ctx->ranges),
@@ -716,6 +768,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   ctx->last_views = n_views;
   ctx->last_inst_tile = inst_tile;
   ctx->last_inst_val = inst_val;
+  ctx->last_by_cell = by_cell;
 
   if (state_out) {
     // hand the buffers the backward re-reads to a new state; the context
@@ -934,7 +987,7 @@ nxs_status nxs_forward_status(nxs_context* ctx, int64_t* needed) {
                 "the 32-bit range", ds.count, (unsigned long long)ds.need);
   if ((ds.fail & kFailCapacity) && ds.need > instance_capacity(ctx)) {
     // all of the context's work has completed: grow on the null stream
-    nxs_status st = grow_instances(ctx, ds.need, ctx->last_slots, nullptr);
+    nxs_status st = grow_instances(ctx, ds.need, nullptr);
     if (st != NXS_OK) {
       const std::string why = ctx->err;
       return fail(ctx, NXS_ECAPACITY, "%u deferred render(s) failed; growing to %llu "
@@ -1260,6 +1313,17 @@ nxs_status resolve_last_m(nxs_context* ctx, bool* failed) {
   return NXS_OK;
 }
 
+// The last render's tile ranges as they are on the device.
+nxs_status read_ranges(nxs_context* ctx, std::vector<uint2>* out) {
+  const void* src = ctx->last_state ? ctx->last_state->ranges.p : ctx->ranges.p;
+  if (!src) return fail(ctx, NXS_EINVAL, "no render on this context");
+  HIP_TRY(hipSetDevice(ctx->device));
+  HIP_TRY(hipEventSynchronize(ctx->done));
+  out->resize(ctx->last_tiles);
+  HIP_TRY(hipMemcpy(out->data(), src, 8 * ctx->last_tiles, hipMemcpyDeviceToHost));
+  return NXS_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1283,14 +1347,29 @@ nxs_status nxs_inspect_instances(nxs_context* ctx, uint64_t* keys_host, int32_t*
   if ((!keys_host && ctx->last_m) || (!ids_host && ctx->last_m)) return NXS_EINVAL;
   if (capacity < ctx->last_m) return fail(ctx, NXS_EINVAL, "capacity below instance count");
   if (ctx->last_m == 0) return NXS_OK;
-  if (failed || !ctx->last_inst_tile || !ctx->last_inst_val)
+  if (failed || !ctx->last_inst_val ||
+      (ctx->last_by_cell ? !ctx->depth_key.p : !ctx->last_inst_tile))
     return fail(ctx, NXS_EINVAL, "the last render did not complete");
   HIP_TRY(hipSetDevice(ctx->device));
   HIP_TRY(hipEventSynchronize(ctx->done));
   std::vector<uint32_t> tile(ctx->last_m), val(ctx->last_m), dk(ctx->last_slots);
-  HIP_TRY(hipMemcpy(tile.data(), ctx->last_inst_tile, 4 * ctx->last_m, hipMemcpyDeviceToHost));
   HIP_TRY(hipMemcpy(val.data(), ctx->last_inst_val, 4 * ctx->last_m, hipMemcpyDeviceToHost));
   HIP_TRY(hipMemcpy(dk.data(), ctx->depth_key.p, 4 * ctx->last_slots, hipMemcpyDeviceToHost));
+  if (ctx->last_by_cell) {
+    // the tiles' lists, which lie cell by cell, in the order of the tiles
+    std::vector<uint2> rg;
+    if ((st = read_ranges(ctx, &rg)) != NXS_OK) return st;
+    std::vector<uint32_t> by_tile(ctx->last_m);
+    int64_t at = 0;
+    for (int64_t k = 0; k < ctx->last_tiles; ++k)
+      for (uint32_t j = rg[k].x; j < rg[k].y && at < ctx->last_m; ++j, ++at) {
+        tile[at] = (uint32_t)k;
+        by_tile[at] = val[j];
+      }
+    val.swap(by_tile);
+  } else {
+    HIP_TRY(hipMemcpy(tile.data(), ctx->last_inst_tile, 4 * ctx->last_m, hipMemcpyDeviceToHost));
+  }
   for (int64_t j = 0; j < ctx->last_m; ++j) {
     keys_host[j] = ((uint64_t)tile[j] << 32) | dk[val[j]];
     ids_host[j] = (int32_t)(val[j] % (uint32_t)ctx->last_n);
@@ -1301,11 +1380,20 @@ nxs_status nxs_inspect_instances(nxs_context* ctx, uint64_t* keys_host, int32_t*
 nxs_status nxs_inspect_ranges(nxs_context* ctx, int32_t* ranges_host, int64_t capacity) {
   if (!ctx || !ranges_host) return NXS_EINVAL;
   if (capacity < 2 * ctx->last_tiles) return fail(ctx, NXS_EINVAL, "capacity below 2 * tiles");
-  const void* src = ctx->last_state ? ctx->last_state->ranges.p : ctx->ranges.p;
-  if (!src) return fail(ctx, NXS_EINVAL, "no render on this context");
-  HIP_TRY(hipSetDevice(ctx->device));
-  HIP_TRY(hipEventSynchronize(ctx->done));
-  HIP_TRY(hipMemcpy(ranges_host, src, 8 * ctx->last_tiles, hipMemcpyDeviceToHost));
+  std::vector<uint2> rg;
+  nxs_status st = read_ranges(ctx, &rg);
+  if (st != NXS_OK) return st;
+  uint32_t at = 0;
+  for (uint2& r : rg) {
+    // (lists that lie cell by cell: the places they have in the order of the
+    // tiles; an empty tile's range stays [0, 0))
+    if (ctx->last_by_cell && r.x != r.y) {
+      const uint32_t len = r.y - r.x;
+      r = make_uint2(at, at + len);
+      at += len;
+    }
+  }
+  std::memcpy(ranges_host, rg.data(), 8 * ctx->last_tiles);
   return NXS_OK;
 }
 

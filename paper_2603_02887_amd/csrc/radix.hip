@@ -62,6 +62,26 @@ __device__ __forceinline__ ChunkWalk chunk_walk(uint32_t b, uint32_t per_g, uint
   return w;
 }
 
+// Keys in `parts` equal parts of n, each sorted on its own: chunk c holds the
+// keys [first, first + len) of part p, its `col`-th chunk of cpp.  (One part:
+// the whole range; its n may be a device count.)
+struct ChunkPlace {
+  int64_t first;
+  int len;
+  uint32_t part, col;
+};
+template <int ITEMS>
+__device__ __forceinline__ ChunkPlace chunk_place(uint32_t c, uint32_t cpp, int64_t n) {
+  constexpr int CHUNK = kRThreads * ITEMS;
+  ChunkPlace p;
+  p.part = c / cpp;
+  p.col = c - p.part * cpp;
+  const int64_t in = (int64_t)p.col * CHUNK;
+  p.first = (int64_t)p.part * n + in;
+  p.len = (int)min((int64_t)CHUNK, n - in);
+  return p;
+}
+
 // lanes of the wave whose digit equals this lane's (valid lanes only)
 __device__ __forceinline__ uint64_t digit_peers(uint32_t d, int width, bool valid) {
   uint64_t peers = __ballot(valid);
@@ -117,13 +137,14 @@ __global__ __launch_bounds__(kRThreads) void rx_count(const uint32_t* keys,
                                                       const uint32_t* keys_first, int64_t n,
                                                       int shift, int width,
                                                       const uint32_t* __restrict__ plan,
-                                                      int pass, uint32_t nchunks, uint32_t per,
+                                                      int pass, uint32_t parts, uint32_t cpp,
+                                                      uint32_t per,
                                                       uint32_t* __restrict__ counts,
                                                       const Counters* __restrict__ dn) {
   __shared__ uint32_t h[kRBins];
   if (!pass_digit(plan, pass, shift, width)) return;   // the whole grid
   n = key_count(n, dn);
-  const ChunkWalk walk = chunk_walk(blockIdx.x, per, min(nchunks, live_chunks<ITEMS>(n)));
+  const ChunkWalk walk = chunk_walk(blockIdx.x, per, parts * min(cpp, live_chunks<ITEMS>(n)));
   {
     const uint32_t* unused = nullptr;
     select_input(plan, pass, keys_first, nullptr, keys, unused);
@@ -133,8 +154,9 @@ __global__ __launch_bounds__(kRThreads) void rx_count(const uint32_t* keys,
   for (uint32_t c = walk.first; c < walk.end; c += walk.step) {   // (uniform per group)
     for (int d = t; d < kRBins; d += kRThreads) h[d] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)c * (kRThreads * ITEMS);
-    const int chunk_n = (int)min((int64_t)(kRThreads * ITEMS), n - base);
+    const ChunkPlace at = chunk_place<ITEMS>(c, cpp, n);
+    const int64_t base = at.first;
+    const int chunk_n = at.len;
     uint32_t k[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
@@ -149,7 +171,8 @@ __global__ __launch_bounds__(kRThreads) void rx_count(const uint32_t* keys,
       if (valid) atomicAdd(&h[d], 1u);
     }
     __syncthreads();
-    for (int d = t; d <= (int)mask; d += kRThreads) counts[(int64_t)d * nchunks + c] = h[d];
+    for (int d = t; d <= (int)mask; d += kRThreads)
+      counts[((int64_t)at.part * kRBins + d) * cpp + at.col] = h[d];
     __syncthreads();   // h is cleared for the next chunk
   }
 }
@@ -171,8 +194,8 @@ __device__ __forceinline__ uint32_t rx_block_scan(uint32_t x, uint32_t* s_tmp, u
   return off + incl - x;
 }
 
-// One work-group per digit: exclusive scan of counts[d][0..live chunks) in
-// place (rows of nchunks entries).
+// One work-group per part (blockIdx.y) and digit: exclusive scan of
+// counts[part][d][0..live chunks) in place (rows of nchunks entries).
 template <int ITEMS>
 __global__ __launch_bounds__(kRThreads) void rx_scan(uint32_t* __restrict__ counts,
                                                      uint32_t nchunks,
@@ -184,7 +207,8 @@ __global__ __launch_bounds__(kRThreads) void rx_scan(uint32_t* __restrict__ coun
   int shift = 0;
   if (!pass_digit(plan, pass, shift, width)) return;   // the whole grid
   if (blockIdx.x >= (1u << width)) return;    // the whole work-group
-  uint32_t* row = counts + (int64_t)blockIdx.x * nchunks;
+  const uint32_t out = blockIdx.y * kRBins + blockIdx.x;
+  uint32_t* row = counts + (int64_t)out * nchunks;
   nchunks = min(nchunks, live_chunks<ITEMS>(key_count(n, dn)));
   uint32_t running = 0;
   for (uint32_t b = 0; b < nchunks; b += kRThreads * 4) {
@@ -205,18 +229,18 @@ __global__ __launch_bounds__(kRThreads) void rx_scan(uint32_t* __restrict__ coun
     }
     running += tot;
   }
-  if (threadIdx.x == 0) totals[blockIdx.x] = running;
+  if (threadIdx.x == 0) totals[out] = running;
 }
 
 // vals_in == nullptr: the values are the input positions.  The last pass
-// also writes each value's tile rectangle (from `trect`) and tile count when
-// trect is given.
+// also writes each value's tile rectangle (from `trect`) when trect is given,
+// and its tile count when nt_out is.
 template <int ITEMS>
 __global__ __launch_bounds__(kRThreads) void rx_scatter(
     const uint32_t* keys_in, const uint32_t* vals_in, const uint32_t* keys_first,
     const uint32_t* vals_first, uint32_t* __restrict__ keys_out,
     uint32_t* __restrict__ vals_out, int64_t n, int shift, int width,
-    const uint32_t* __restrict__ plan, int pass, uint32_t nchunks, uint32_t per,
+    const uint32_t* __restrict__ plan, int pass, uint32_t parts, uint32_t cpp, uint32_t per,
     const uint32_t* __restrict__ counts, const uint32_t* __restrict__ totals,
     const uint2* __restrict__ trect, uint32_t* __restrict__ nt_out,
     uint2* __restrict__ rect_out, const Counters* __restrict__ dn) {
@@ -232,7 +256,7 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
 
   if (!pass_digit(plan, pass, shift, width)) return;   // the whole grid
   n = key_count(n, dn);
-  const ChunkWalk walk = chunk_walk(blockIdx.x, per, min(nchunks, live_chunks<ITEMS>(n)));
+  const ChunkWalk walk = chunk_walk(blockIdx.x, per, parts * min(cpp, live_chunks<ITEMS>(n)));
   select_input(plan, pass, keys_first, vals_first, keys_in, vals_in);
   const int t = threadIdx.x;
   const int lane = t & 63, wid = t >> 6;
@@ -241,8 +265,9 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
   static_assert(sizeof(s_wave) == 16 * kRThreads, "one 16-byte store per thread clears s_wave");
   for (uint32_t c = walk.first; c < walk.end; c += walk.step) {   // (uniform per group)
     reinterpret_cast<uint4*>(&s_wave[0][0])[t] = make_uint4(0u, 0u, 0u, 0u);
-    const int64_t base = (int64_t)c * (kRThreads * ITEMS);
-    const int chunk_n = (int)min((int64_t)(kRThreads * ITEMS), n - base);
+    const ChunkPlace at = chunk_place<ITEMS>(c, cpp, n);
+    const int64_t base = at.first;
+    const int chunk_n = at.len;
 
     uint32_t k_reg[ITEMS], v_reg[ITEMS];
 #pragma unroll
@@ -261,30 +286,46 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
     const int d0 = 2 * t, d1 = 2 * t + 1;
     uint32_t gbase0, gbase1;
     {
-      const uint32_t tot0 = d0 < nd ? totals[d0] : 0u, tot1 = d1 < nd ? totals[d1] : 0u;
-      const uint32_t off0 = d0 < nd ? counts[(int64_t)d0 * nchunks + c] : 0u;
-      const uint32_t off1 = d1 < nd ? counts[(int64_t)d1 * nchunks + c] : 0u;
+      const uint32_t row = at.part * kRBins;
+      const uint32_t tot0 = d0 < nd ? totals[row + d0] : 0u;
+      const uint32_t tot1 = d1 < nd ? totals[row + d1] : 0u;
+      const uint32_t off0 = d0 < nd ? counts[(int64_t)(row + d0) * cpp + at.col] : 0u;
+      const uint32_t off1 = d1 < nd ? counts[(int64_t)(row + d1) * cpp + at.col] : 0u;
       uint32_t all;
-      const uint32_t ex = rx_block_scan(tot0 + tot1, s_tmp, &all);
+      const uint32_t ex =
+          (uint32_t)(at.part * n) + rx_block_scan(tot0 + tot1, s_tmp, &all);
       gbase0 = ex + off0;
       gbase1 = ex + tot0 + off1;
     }
-    // per-wave ranks: keys of the same digit earlier in this wave's part
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // per-wave ranks: keys of the same digit earlier in this wave's part (in
+    // groups of four, whose matching overlaps)
     uint32_t rank[ITEMS], dig[ITEMS];
+    constexpr int G = ITEMS < 4 ? ITEMS : 4;
+    static_assert(ITEMS % G == 0, "whole groups");
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-      const int li = wid * (64 * ITEMS) + r * 64 + lane;
-      const bool valid = li < chunk_n;
-      const uint32_t d = valid ? (k_reg[r] >> shift) & mask : 0u;
-      const uint64_t peers = digit_peers(d, width, valid);
-      dig[r] = d;
-      rank[r] = 0;
-      if (valid) {
-        const uint32_t before = s_wave[wid][d];   // the same for every peer
-        const uint32_t pos = (uint32_t)__popcll(peers & lt_mask);
-        rank[r] = before + pos;
-        if (pos == 0) s_wave[wid][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+    for (int r0 = 0; r0 < ITEMS; r0 += G) {
+      uint32_t d[G], lo[G], hi[G];
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const int li = wid * (64 * ITEMS) + (r0 + q) * 64 + lane;
+        d[q] = (k_reg[r0 + q] >> shift) & mask;   // (0 for an invalid key)
+        const uint64_t m = __ballot(li < chunk_n);
+        lo[q] = (uint32_t)m;
+        hi[q] = (uint32_t)(m >> 32);
+      }
+      match_digits<G>(d, width, lo, hi);
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const int li = wid * (64 * ITEMS) + (r0 + q) * 64 + lane;
+        dig[r0 + q] = d[q];
+        rank[r0 + q] = 0;
+        if (li < chunk_n) {
+          const uint32_t before = s_wave[wid][d[q]];   // the same for every peer
+          const uint32_t pos = lanes_below(lo[q], hi[q]);
+          rank[r0 + q] = before + pos;
+          if (pos == 0)
+            s_wave[wid][d[q]] = (uint16_t)(before + (uint32_t)(__popc(lo[q]) + __popc(hi[q])));
+        }
       }
     }
     __syncthreads();
@@ -334,7 +375,7 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
         vals_out[g] = v;
         if (trect) {   // the slot's tile rectangle, now in sorted order
           const uint2 rc = trect[v];
-          nt_out[g] = rect_tile_count(rc);
+          if (nt_out) nt_out[g] = rect_tile_count(rc);
           rect_out[g] = rc;
         }
       }
@@ -697,9 +738,9 @@ __global__ __launch_bounds__(kRThreads) void tile_depth_sort_kernel(
 
 }  // namespace
 
-size_t radix_counts_words(int64_t n) {
+size_t radix_counts_words(int64_t n, int parts) {
   const int64_t nchunks = std::max<int64_t>((n + kRChunkMin - 1) / kRChunkMin, 1);
-  return (size_t)nchunks * kRBins + kRBins;
+  return ((size_t)nchunks * kRBins + kRBins) * parts;
 }
 
 namespace {
@@ -711,41 +752,41 @@ int run_passes(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
                uint32_t* k1, uint32_t* v1, int64_t n, int first, int passes,
                const int* shifts, const int* widths, const uint32_t* plan, uint32_t* counts,
                const uint2* trect, uint32_t* nt_out, uint2* rect_out, hipStream_t s,
-               const Counters* dn, int64_t n_plan) {
-  // n bounds the keys (the counts layout); the grid is planned for n_plan
+               const Counters* dn, int64_t n_plan, int parts = 1) {
+  // n (per part) bounds the keys (the counts layout); the grid is planned for n_plan
   // keys (with dn, the count expected on the device) and loops beyond it
-  const bool large = n_plan >= kRLargeFrom;
+  const bool large = n_plan * parts >= kRLargeFrom;
   const int chunk = kRThreads * (large ? kRItemsLarge : kRItemsSmall);
   const uint32_t nchunks = (uint32_t)((n + chunk - 1) / chunk);
   const uint32_t plan_chunks =
       (uint32_t)std::max<int64_t>((std::min(n_plan, n) + chunk - 1) / chunk, 1);
-  const uint32_t per = (plan_chunks + kRXcds - 1) / kRXcds;
+  const uint32_t per = (plan_chunks * parts + kRXcds - 1) / kRXcds;
   const unsigned grid = per * kRXcds;
-  uint32_t* totals = counts + (size_t)nchunks * kRBins;
+  uint32_t* totals = counts + (size_t)nchunks * kRBins * parts;
   const uint32_t* kin = keys_in;
   const uint32_t* vin = vals_in;
   for (int p = first; p < passes; ++p) {
     const int shift = shifts ? shifts[p] : 0, width = widths ? widths[p] : 8;
     uint32_t* kout = (p & 1) ? k1 : k0;
     uint32_t* vout = (p & 1) ? v1 : v0;
-    const dim3 scan_grid(plan ? kRBins : (1u << width));
+    const dim3 scan_grid(plan ? kRBins : (1u << width), parts);
     const bool last = p == passes - 1;
     if (large) {
       hipLaunchKernelGGL(rx_count<kRItemsLarge>, dim3(grid), dim3(kRThreads), 0, s, kin,
-                         keys_in, n, shift, width, plan, p, nchunks, per, counts, dn);
+                         keys_in, n, shift, width, plan, p, (uint32_t)parts, nchunks, per, counts, dn);
       hipLaunchKernelGGL(rx_scan<kRItemsLarge>, scan_grid, dim3(kRThreads), 0, s, counts,
                          nchunks, totals, width, plan, p, n, dn);
       hipLaunchKernelGGL(rx_scatter<kRItemsLarge>, dim3(grid), dim3(kRThreads), 0, s, kin, vin,
-                         keys_in, vals_in, kout, vout, n, shift, width, plan, p, nchunks, per,
-                         counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
+                         keys_in, vals_in, kout, vout, n, shift, width, plan, p,
+                         (uint32_t)parts, nchunks, per, counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
     } else {
       hipLaunchKernelGGL(rx_count<kRItemsSmall>, dim3(grid), dim3(kRThreads), 0, s, kin,
-                         keys_in, n, shift, width, plan, p, nchunks, per, counts, dn);
+                         keys_in, n, shift, width, plan, p, (uint32_t)parts, nchunks, per, counts, dn);
       hipLaunchKernelGGL(rx_scan<kRItemsSmall>, scan_grid, dim3(kRThreads), 0, s, counts,
                          nchunks, totals, width, plan, p, n, dn);
       hipLaunchKernelGGL(rx_scatter<kRItemsSmall>, dim3(grid), dim3(kRThreads), 0, s, kin, vin,
-                         keys_in, vals_in, kout, vout, n, shift, width, plan, p, nchunks, per,
-                         counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
+                         keys_in, vals_in, kout, vout, n, shift, width, plan, p,
+                         (uint32_t)parts, nchunks, per, counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
     }
     kin = kout;
     vin = vout;
@@ -773,12 +814,12 @@ int radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
 }
 
 int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0,
-                       uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n,
+                       uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int parts,
                        const uint32_t* plan, int first_pass, uint32_t* counts,
                        const uint2* trect, uint32_t* nt_out, uint2* rect_out, hipStream_t s) {
   if (n <= 0) return 1;
   return run_passes(keys_in, vals_in, k0, v0, k1, v1, n, first_pass, kPlanPasses, nullptr,
-                    nullptr, plan, counts, trect, nt_out, rect_out, s, nullptr, n);
+                    nullptr, plan, counts, trect, nt_out, rect_out, s, nullptr, n, parts);
 }
 
 void launch_tile_depth_sort(const uint2* ranges, int64_t n_tiles, const uint32_t* depth_key,
