@@ -76,7 +76,7 @@ struct nxs_context {
   // workspace
   DevBuf views, counters, partials, status;
   DevBuf depth_key, dsort_a, dsort_b, slot_a, slot_b, trect, nt_sorted, rect_sorted, prec;
-  DevBuf scan_local, block_sums, counts, cells, segs;
+  DevBuf scan_local, block_sums, counts, cells, segs, vis;
   DevBuf inst_tile, inst_tile_alt, inst_val, inst_val_alt;
   DevBuf ranges, pstate, gslot, order;
   int n_cu = 256;
@@ -230,7 +230,7 @@ void free_workspace(nxs_context* ctx, hipStream_t s) {
                     &ctx->prec,       &ctx->scan_local, &ctx->block_sums,   &ctx->counts,
                     &ctx->inst_tile,  &ctx->inst_tile_alt, &ctx->inst_val,  &ctx->inst_val_alt,
                     &ctx->ranges,     &ctx->pstate,    &ctx->gslot,         &ctx->order,
-                    &ctx->cells,      &ctx->segs};
+                    &ctx->cells,      &ctx->segs,      &ctx->vis};
   for (DevBuf* b : list) drop(ctx, *b, s, true);
   ctx->ws_total = 0;
   ctx->status_clear = false;
@@ -566,7 +566,15 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
                                                      : (double)ctx->m_hint;
     tile_first = expect > 0.0 && expect <= kAutoTileFirstPerTile * (double)total_tiles;
   }
-  const int depth_first = (ctx->noalloc || tile_first) ? 0 : ctx->depth_first;
+  // small views are sorted by depth in LDS; vis: visible slots per view, the
+  // only ones sorted then
+  const bool in_lds = by_cell && !tile_first && g->n > 0 && g->n <= kLocalMax;
+  uint32_t* vis = nullptr;
+  if (in_lds) {
+    if ((st = ensure(ctx, ctx->vis, 4 * (size_t)n_views, s))) return st;
+    vis = P<uint32_t>(ctx->vis);
+  }
+  const int depth_first = (ctx->noalloc || tile_first || in_lds) ? 0 : ctx->depth_first;
   // (the fold writes the counters, or a deferred render's status, straight
   // into the context's pinned memory; the no-alloc call copies them)
   DeferCheck chk{~0ull, 0, nullptr, nullptr, ctx->noalloc ? nullptr : ctx->host_counters};
@@ -602,6 +610,13 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   //    (launched from the pass the last render's plan needed; checked below,
   //    or on the device for a deferred render)
   auto depth_sort = [&](int first) {
+    if (in_lds) {
+      launch_depth_local(proj.depth_key, proj.trect, g->n, n_views, P<uint32_t>(ctx->dsort_a),
+                         P<uint32_t>(ctx->slot_a), P<uint32_t>(ctx->dsort_b),
+                         P<uint32_t>(ctx->slot_b), vis, P<uint32_t>(ctx->slot_b),
+                         P<uint2>(ctx->rect_sorted), s);
+      return 1;
+    }
     return radix_sort_planned(P<uint32_t>(ctx->depth_key), nullptr, P<uint32_t>(ctx->dsort_a),
                               P<uint32_t>(ctx->slot_a), P<uint32_t>(ctx->dsort_b),
                               P<uint32_t>(ctx->slot_b), S / sort_parts, sort_parts,
@@ -625,7 +640,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
                 nullptr, P<uint2>(ctx->ranges)};
   auto count_slots = [&]() {
     if (by_cell)
-      launch_bin_count(bins, bb, rects, dviews, dcount, s);
+      launch_bin_count(bins, bb, rects, vis, dviews, dcount, s);
     else
       launch_emit_scan(tile_first ? nullptr : P<uint32_t>(ctx->nt_sorted), proj.trect, S,
                        P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums), s);
@@ -634,7 +649,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     if (by_cell) {
       bb.pair_slot = P<uint32_t>(ctx->inst_tile);
       bb.pair_rect = P<uint16_t>(ctx->inst_tile_alt);
-      launch_bin_scatter(bins, bb, sorted_slots, rects, dviews, cap, dcount, s);
+      launch_bin_scatter(bins, bb, sorted_slots, rects, vis, dviews, cap, dcount, s);
     } else {
       launch_emit_write(sorted_slots, tile_first ? nullptr : rects, proj.trect, S, g->n, dviews,
                         P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums),
@@ -660,7 +675,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     // the depth sort skipped pass 0 but this render's plan needs it: sort and
     // bin again below (the depth keys are intact)
     const bool pass0 = (ctx->host_counters->plan[0] & kPassActive) != 0;
-    const bool resort = !tile_first && S > 0 && depth_first == 1 && pass0;
+    const bool resort = !tile_first && !in_lds && S > 0 && depth_first == 1 && pass0;
     if (!ctx->noalloc) ctx->depth_first = pass0 ? 0 : 1;
     // what this render needs, visible through nxs_inspect_counts even if it fails
     ctx->last_m = (int64_t)M;

@@ -46,7 +46,6 @@ constexpr int kBWaves = kBThreads / 64;
 constexpr uint32_t kShortRun = 8;    // slots of more cells are taken by a whole wave
 constexpr uint32_t kXcds = 8;
 constexpr int kStartThreads = 1024;
-constexpr int64_t kSmallest = 8192;
 constexpr int kMinChunk = 256;
 constexpr int64_t kWantChunks = 768;
 // Slots from which segments take 256 and 1,024 pairs instead of 64: a wave goes
@@ -125,12 +124,13 @@ struct ChunkOf {
   uint32_t col, cell0, cells_x, n_cells;
 };
 __device__ __forceinline__ ChunkOf chunk_of(uint32_t c, uint32_t cpv, uint32_t chunk, int32_t n,
+                                            const uint32_t* __restrict__ vis,
                                             const ViewDev* __restrict__ views, int sy) {
   ChunkOf k;
   const uint32_t vi = c / cpv;
   k.col = c - vi * cpv;
   k.first = (int64_t)vi * n + (int64_t)k.col * chunk;
-  k.end = min(k.first + chunk, (int64_t)(vi + 1) * n);
+  k.end = min(k.first + chunk, (int64_t)vi * n + (vis ? (int64_t)vis[vi] : (int64_t)n));
   const ViewDev& v = views[vi];
   k.cell0 = (uint32_t)v.cell_off;
   k.cells_x = (uint32_t)v.cells_x;
@@ -139,14 +139,14 @@ __device__ __forceinline__ ChunkOf chunk_of(uint32_t c, uint32_t cpv, uint32_t c
 }
 
 __global__ __launch_bounds__(kBThreads) void cell_count_kernel(
-    const uint2* __restrict__ rects, int32_t n, uint32_t nchunks, uint32_t cpv, uint32_t chunk,
-    uint32_t per, const ViewDev* __restrict__ views, int sx, int sy,
+    const uint2* __restrict__ rects, int32_t n, const uint32_t* __restrict__ vis,
+    uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per, const ViewDev* __restrict__ views, int sx, int sy,
     uint32_t* __restrict__ counts, const Counters* __restrict__ cnt) {
   __shared__ uint32_t h[kViewCells];
   if (cnt->fail) return;
   const uint32_t c = banded_chunk(blockIdx.x, per);
   if (c >= nchunks) return;
-  const ChunkOf ck = chunk_of(c, cpv, chunk, n, views, sy);
+  const ChunkOf ck = chunk_of(c, cpv, chunk, n, vis, views, sy);
   const int lane = threadIdx.x & 63;
   for (uint32_t d = threadIdx.x; d < ck.n_cells; d += kBThreads) h[d] = 0u;
   __syncthreads();
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kStartThreads) void cell_starts_kernel(
 template <int kSubPerT, int kWinItems>
 __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
     const uint32_t* __restrict__ sorted_slots, const uint2* __restrict__ rects, int32_t n,
-    uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per,
+    const uint32_t* __restrict__ vis, uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per,
     const ViewDev* __restrict__ views, int sx, int sy, const uint32_t* __restrict__ counts,
     const uint32_t* __restrict__ pair0, uint64_t capacity, uint32_t* __restrict__ pair_slot,
     uint16_t* __restrict__ pair_rect, const Counters* __restrict__ cnt) {
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
   if (cnt->fail || cnt->total > capacity) return;
   const uint32_t c = banded_chunk(blockIdx.x, per);
   if (c >= nchunks) return;
-  const ChunkOf ck = chunk_of(c, cpv, chunk, n, views, sy);
+  const ChunkOf ck = chunk_of(c, cpv, chunk, n, vis, views, sy);
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   const int width = 32 - __clz((int)(ck.n_cells - 1u));   // bits of a cell (0: one cell)
 #pragma unroll
@@ -645,9 +645,6 @@ BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, i
   BinPlan p{};
   p.n = n;
   p.n_views = n_views;
-  // (a few thousand slots: three short kernels more than sorting the
-  // instances, and nothing to gain: 118 against 113 us for a render of 4,096)
-  if ((int64_t)n * n_views < kSmallest) return p;
   for (int k = 0; k < 3 && n_views <= kMaxBinViews && !p.n_cells; ++k) {
     p.sx = shapes[k][0];
     p.sy = shapes[k][1];
@@ -713,11 +710,12 @@ void fine_t(const BinPlan& p, const BinBuffers& b, uint64_t m_plan, const ViewDe
 }  // namespace
 
 void launch_bin_count(const BinPlan& p, const BinBuffers& b, const uint2* rects,
-                      const ViewDev* views, const Counters* counters, hipStream_t s) {
+                      const uint32_t* vis, const ViewDev* views, const Counters* counters,
+                      hipStream_t s) {
   if (p.n <= 0) return;
   const CellArrays a = cell_arrays(p, b);
   const uint32_t nchunks = p.cpv * p.n_views, per = (nchunks + kXcds - 1) / kXcds;
-  hipLaunchKernelGGL(cell_count_kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, rects, p.n,
+  hipLaunchKernelGGL(cell_count_kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, rects, p.n, vis,
                      nchunks, p.cpv, (uint32_t)p.chunk, per, views, p.sx, p.sy, b.counts,
                      counters);
   hipLaunchKernelGGL(cell_scan_kernel, dim3(p.n_cells), dim3(kBThreads), 0, s, b.counts, p.cpv,
@@ -727,13 +725,13 @@ void launch_bin_count(const BinPlan& p, const BinBuffers& b, const uint2* rects,
 }
 
 void launch_bin_scatter(const BinPlan& p, const BinBuffers& b, const uint32_t* sorted_slots,
-                        const uint2* rects, const ViewDev* views, uint64_t capacity,
-                        const Counters* counters, hipStream_t s) {
+                        const uint2* rects, const uint32_t* vis, const ViewDev* views,
+                        uint64_t capacity, const Counters* counters, hipStream_t s) {
   if (p.n <= 0) return;
   const CellArrays a = cell_arrays(p, b);
   const uint32_t nchunks = p.cpv * p.n_views, per = (nchunks + kXcds - 1) / kXcds;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, sorted_slots, rects, p.n,
+    hipLaunchKernelGGL(kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, sorted_slots, rects, p.n, vis,
                        nchunks, p.cpv, (uint32_t)p.chunk, per, views, p.sx, p.sy, b.counts,
                        a.pair0, capacity, b.pair_slot, b.pair_rect, counters);
   };

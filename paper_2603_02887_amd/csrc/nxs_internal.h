@@ -106,6 +106,34 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan_u32(uint32_t x) {
   return (uint32_t)v;
 }
 
+// A wave's reduction under an associative, commutative op (every lane active):
+// within each 16-lane row by four DPP row shifts (a lane whose source lies
+// before its row combines the identity), then the four rows' last lanes,
+// read by readlane; the result is the same on every lane.
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t x, uint32_t identity, Op op) {
+  const int id = (int)identity;
+  uint32_t v = x;
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x111, 0xF, 0xF, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x112, 0xF, 0xF, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x114, 0xF, 0xF, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)v, 0x118, 0xF, 0xF, false));
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+  const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
+  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+  const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+  return op(op(r0, r1), op(r2, r3));
+}
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+  return wave_reduce_u32(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
+  return wave_reduce_u32(x, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  return wave_reduce_u32(x, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+}
+
 // For each of ITEMS digits per lane: the lanes of the wave whose digit equals
 // this lane's (width bits; lo / hi hold the valid lanes on entry).  Per bit and
 // digit one bit extract, one compare whose mask is the ballot, and two
@@ -202,6 +230,16 @@ int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
                        const uint32_t* plan, int first_pass, uint32_t* counts,
                        const uint2* trect, uint32_t* nt_out, uint2* rect_out, hipStream_t s);
 
+// Depth sort of views of n <= kLocalMax slots each, one work-group per view
+// (depth.hip), stable: the slots of view v's visible Gaussians and their tile
+// rectangles in order, from v * n on, and vis[v] how many there are.  The
+// temporaries hold a slot each (slot_alt may be slots_out).
+constexpr int kLocalMax = 8192;
+void launch_depth_local(const uint32_t* depth_key, const uint2* trect, int32_t n, int n_views,
+                        uint32_t* key_tmp, uint32_t* slot_tmp, uint32_t* key_alt,
+                        uint32_t* slot_alt, uint32_t* vis, uint32_t* slots_out, uint2* rect_out,
+                        hipStream_t s);
+
 // Binning in two levels (bin.hip): each view's slots, in depth order or in slot
 // order (sorted_slots null), are dealt to cells of 2^sx x 2^sy tiles, and each
 // cell's list is expanded into its tiles' lists.  The lists hold the slots in
@@ -236,13 +274,14 @@ size_t bin_counts_words(const BinPlan& p);
 size_t bin_cells_words(const BinPlan& p);
 size_t bin_seg_words(const BinPlan& p, uint64_t max_pairs);
 // Pairs per chunk and cell, and their first positions.
+// (vis: the slots of each view to take, the first of its part; null: all)
 void launch_bin_count(const BinPlan& p, const BinBuffers& b, const uint2* rects,
-                      const ViewDev* views, const Counters* counters, hipStream_t s);
+                      const uint32_t* vis, const ViewDev* views, const Counters* counters, hipStream_t s);
 // The pairs into their cells' lists; nothing if the render has more than
 // `capacity` instances.
 void launch_bin_scatter(const BinPlan& p, const BinBuffers& b, const uint32_t* sorted_slots,
-                        const uint2* rects, const ViewDev* views, uint64_t capacity,
-                        const Counters* counters, hipStream_t s);
+                        const uint2* rects, const uint32_t* vis, const ViewDev* views,
+                        uint64_t capacity, const Counters* counters, hipStream_t s);
 // The cells' lists into the tiles' (grids for m_plan instances).
 void launch_bin_tiles(const BinPlan& p, const BinBuffers& b, uint64_t m_plan,
                       const ViewDev* views, const Counters* counters, hipStream_t s);
