@@ -312,18 +312,33 @@ __global__ __launch_bounds__(kOrderThreads) void order_rank_kernel(
 __global__ __launch_bounds__(kOrderThreads) void order_scatter_kernel(
     const uint2* __restrict__ ranges, uint32_t n_tiles, const uint32_t* __restrict__ buckets,
     const uint32_t* __restrict__ rank, uint32_t* __restrict__ order) {
-  __shared__ uint32_t start[kBuckets];
+  __shared__ uint32_t start[kBuckets + 1];
   const uint32_t t = threadIdx.x;
   if (t == 0) {
     uint32_t run = 0;
     for (int k = kBuckets - 1; k >= 0; --k) {   // longest lists first
-      start[k] = run;
+      start[k + 1] = run;
       run += buckets[k];
     }
+    start[0] = run;
   }
   __syncthreads();
   const uint32_t i = blockIdx.x * kOrderThreads + t;
-  if (i < n_tiles) order[start[length_bucket(ranges[i])] + rank[i]] = i;
+  if (i >= n_tiles) return;
+  const uint32_t k = length_bucket(ranges[i]);
+  // Place `at` of the order runs on XCD at % 8.  Ranks follow the tiles' own
+  // order roughly (64 at a time), so a bucket's whole rows of eight are dealt
+  // out in eight contiguous parts rather than tile by tile: neighbouring tiles,
+  // which share most of their records, then meet in one L2.
+  const uint32_t at = start[k + 1] + rank[i];
+  const uint32_t lo = (start[k + 1] + kQueues - 1) / kQueues * kQueues;
+  const uint32_t hi = start[k] / kQueues * kQueues;
+  uint32_t to = at;
+  if (at >= lo && at < hi) {
+    const uint32_t rows = (hi - lo) / kQueues, p = at - lo;
+    to = lo + p % rows * kQueues + p / rows;
+  }
+  order[to] = i;
 }
 
 }  // namespace
