@@ -574,7 +574,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     if ((st = ensure(ctx, ctx->vis, 4 * (size_t)n_views, s))) return st;
     vis = P<uint32_t>(ctx->vis);
   }
-  const int depth_first = (ctx->noalloc || tile_first || in_lds) ? 0 : ctx->depth_first;
+  // (a deferred render reports a change of plan whichever sort it takes)
+  const int depth_first = (ctx->noalloc || tile_first) ? 0 : ctx->depth_first;
   // (the fold writes the counters, or a deferred render's status, straight
   // into the context's pinned memory; the no-alloc call copies them)
   DeferCheck chk{~0ull, 0, nullptr, nullptr, ctx->noalloc ? nullptr : ctx->host_counters};
