@@ -119,6 +119,8 @@ struct nxs_context {
   uint32_t* last_inst_val = nullptr;
   // the tile lists lie cell by cell (two-level binning; no tile keys are kept)
   bool last_by_cell = false;
+  int last_ax = 0, last_ay = 0;      // its rectangles: tiles of 2^ax x 2^ay units
+  uint32_t last_slot_mask = ~0u;     // the bits of its list entries that are the slot
   const nxs_fwd_state* last_state = nullptr;   // holds last_inst_val, if any
   // instances of the context's last known render: a deferred render's tile
   // sort and ranges are launched for about this many (and loop beyond it)
@@ -469,8 +471,10 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     grid_xy[v] = (cams[v].width + tw - 1) / tw;
     grid_xy[n_views + v] = (cams[v].height + th - 1) / th;
   }
-  const BinPlan bins = plan_bins(grid_xy.data(), grid_xy.data() + n_views, n_views, g->n);
+  const BinPlan bins = plan_bins(grid_xy.data(), grid_xy.data() + n_views, n_views, g->n, tw, th);
   const bool by_cell = bins.n_cells > 0;
+  const uint32_t slot_mask = by_cell && bins.pack ? kPackMask : ~0u;
+  const int ax = by_cell ? bins.ax : 0, ay = by_cell ? bins.ay : 0;
   const int sort_parts = by_cell ? n_views : 1;   // each view's slots on their own
   int64_t off = 0, pix_off = 0, cell_off = 0;
   for (int v = 0; v < n_views; ++v) {
@@ -585,7 +589,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   // (also clears the tile ranges and, after them, the composite schedules'
   // counters)
   if (!launch_project(gd, P<ViewDev>(ctx->views), by_arg ? host_views : nullptr, n_views,
-                      kappa2, c.alpha_min, tw, th, proj, P<uint4>(ctx->partials), dcount, chk,
+                      kappa2, c.alpha_min, bit_length((uint64_t)tw) - 1 - ax,
+                      bit_length((uint64_t)th) - 1 - ay, ax, ay, proj, P<uint4>(ctx->partials), dcount, chk,
                       P<uint32_t>(ctx->ranges), 2 * total_tiles + kSchedCounters, s))
     return fail(ctx, NXS_EHIP, "the view table could not be passed to the projection");
   HIP_TRY(hipGetLastError());
@@ -743,7 +748,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   //     buffer the binning left free
   if (M > 0 && tile_first)
     launch_tile_depth_sort(P<uint2>(ctx->ranges), total_tiles, P<uint32_t>(ctx->depth_key),
-                           dcount, inst_val,
+                           dcount, slot_mask, inst_val,
                            list_alt ? P<uint32_t>(ctx->inst_val) : P<uint32_t>(ctx->inst_val_alt),
                            s);
   // 4b. the tile order of the queue schedules (longest tile lists first)
@@ -771,6 +776,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   cp.param = c.param;
   for (int k = 0; k < 3; ++k) cp.bg[k] = opts->background[k];
   cp.lds_batch = c.batch;
+  cp.slot_mask = slot_mask;
   HIP_TRY(mark(6));
   // 5. composite (also writes the background where no splat lands)
   launch_composite(opts->model, cl, cp, pstate, s);
@@ -785,6 +791,9 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   ctx->last_inst_tile = inst_tile;
   ctx->last_inst_val = inst_val;
   ctx->last_by_cell = by_cell;
+  ctx->last_ax = ax;
+  ctx->last_ay = ay;
+  ctx->last_slot_mask = slot_mask;
 
   if (state_out) {
     // hand the buffers the backward re-reads to a new state; the context
@@ -1387,6 +1396,7 @@ nxs_status nxs_inspect_instances(nxs_context* ctx, uint64_t* keys_host, int32_t*
     HIP_TRY(hipMemcpy(tile.data(), ctx->last_inst_tile, 4 * ctx->last_m, hipMemcpyDeviceToHost));
   }
   for (int64_t j = 0; j < ctx->last_m; ++j) {
+    val[j] &= ctx->last_slot_mask;
     keys_host[j] = ((uint64_t)tile[j] << 32) | dk[val[j]];
     ids_host[j] = (int32_t)(val[j] % (uint32_t)ctx->last_n);
   }
@@ -1445,6 +1455,7 @@ nxs_status nxs_inspect_projection(nxs_context* ctx, int32_t view, uint32_t* dept
       depth_bits_host[i] = 0;
       for (int k = 0; k < 4; ++k) rect_host[4 * i + k] = -1;
     } else {
+      rect[i] = tile_rect(rect[i], ctx->last_ax, ctx->last_ay);
       rect_host[4 * i + 0] = (int32_t)(rect[i].x & 0xFFFF);
       rect_host[4 * i + 1] = (int32_t)(rect[i].x >> 16);
       rect_host[4 * i + 2] = (int32_t)(rect[i].y & 0xFFFF);

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
   StageFetch fetched{};
   if (rg.x < rg.y) {
     slots = stage_slot(inst_val, rg.x, rg.y, lane);
-    fetched = stage_records(slots, rec);
+    fetched = stage_records(slots, rec, prm.slot_mask, wid);
     slots = stage_slot(inst_val, (uint64_t)rg.x + 64, rg.y, lane);
   }
   // the pending splats' sums: lane r < 9 pend adds row r and issues its atomic
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
   };
   for (uint32_t base = rg.x; base < rg.y && act != 0; base += 64) {
     const uint32_t n = stage_batch(fetched, stage_shrink(sb, act), wlds);
-    fetched = stage_records(slots, rec);                              // batch base + 64
+    fetched = stage_records(slots, rec, prm.slot_mask, wid);                              // batch base + 64
     slots = stage_slot(inst_val, (uint64_t)base + 128, rg.y, lane);   // batch base + 128
     for (uint32_t k = 0; k < n && act != 0; ++k) {
       const float4 q0 = wlds[3 * k + 0], q1 = wlds[3 * k + 1], q2 = wlds[3 * k + 2];

@@ -16,8 +16,9 @@
 //   cell_tiles    per cell: first list position of every (segment, tile), and
 //                 the tile ranges
 //   seg_emit      64 pairs at a time: each tile takes, by one ballot over the
-//                 pairs' tile masks, the slots that cover it, and writes them
-//                 as one run at its position
+//                 pairs' blocks in it, the slots that cover it, and writes them
+//                 as one run at its position, each with the 8x8 blocks of the
+//                 tile it covers (the composite's waves fetch by them)
 //
 // Every instance is written once, as the 4-byte slot of its list entry, and
 // never sorted: the pairs that are moved by cell number one to three per slot.
@@ -85,28 +86,40 @@ __device__ __forceinline__ uint32_t banded_chunk(uint32_t b, uint32_t per) {
   return (b % kXcds) * per + b / kXcds;
 }
 
-// The cells a slot's tile rectangle covers, in its view's grid of cells.
+// A cell's extent: log2 of its 8x8 blocks per row and column, and of a tile's.
+struct CellShape {
+  int bx, by, ax, ay;
+};
+
+// The cells a slot's rectangle covers, in its view's grid of cells.
 struct CellSpan {
   uint32_t cx0, cy0, nx, n;   // first cell, cells per row, cells (0: culled)
 };
-__device__ __forceinline__ CellSpan cell_span(uint2 r, int sx, int sy) {
+__device__ __forceinline__ CellSpan cell_span(uint2 r, const CellShape& s) {
   CellSpan c{0u, 0u, 1u, 0u};
   if (r.x == 0xFFFFFFFFu) return c;
-  c.cx0 = (r.x & 0xFFFFu) >> sx;
-  c.cy0 = (r.y & 0xFFFFu) >> sy;
-  c.nx = ((r.x >> 16) >> sx) - c.cx0 + 1u;
-  c.n = c.nx * (((r.y >> 16) >> sy) - c.cy0 + 1u);
+  c.cx0 = (r.x & 0xFFFFu) >> s.bx;
+  c.cy0 = (r.y & 0xFFFFu) >> s.by;
+  c.nx = ((r.x >> 16) >> s.bx) - c.cx0 + 1u;
+  c.n = c.nx * (((r.y >> 16) >> s.by) - c.cy0 + 1u);
   return c;
 }
 
 // The part of the rectangle that lies in cell (cx, cy), in the cell's own
-// tiles: x0 | x1 << 3 | y0 << 6 | y1 << 9.
-__device__ __forceinline__ uint32_t local_rect(uint2 r, uint32_t cx, uint32_t cy, int sx, int sy) {
-  const uint32_t ox = cx << sx, oy = cy << sy;
-  const uint32_t mx = (1u << sx) - 1u, my = (1u << sy) - 1u;
-  const uint32_t x0 = max(r.x & 0xFFFFu, ox) - ox, x1 = min((r.x >> 16) - ox, mx);
-  const uint32_t y0 = max(r.y & 0xFFFFu, oy) - oy, y1 = min((r.y >> 16) - oy, my);
-  return x0 | (x1 << 3) | (y0 << 6) | (y1 << 9);
+// blocks.  (A cell has at most 64 tiles of at most 4 blocks: its four
+// coordinates take at most 16 bits.)
+struct LocalRect {
+  uint32_t x0, x1, y0, y1;
+};
+__device__ __forceinline__ LocalRect local_rect(uint2 r, uint32_t cx, uint32_t cy,
+                                                const CellShape& c) {
+  const uint32_t ox = cx << c.bx, oy = cy << c.by;
+  const uint32_t mx = (1u << c.bx) - 1u, my = (1u << c.by) - 1u;
+  return {max(r.x & 0xFFFFu, ox) - ox, min((r.x >> 16) - ox, mx),
+          max(r.y & 0xFFFFu, oy) - oy, min((r.y >> 16) - oy, my)};
+}
+__device__ __forceinline__ uint32_t pack_rect(const LocalRect& l, const CellShape& c) {
+  return l.x0 | (l.x1 << c.bx) | (l.y0 << (2 * c.bx)) | (l.y1 << (2 * c.bx + c.by));
 }
 
 // l / w for l < 2^24 (float, then exact by the +-1 fix-up)
@@ -125,7 +138,8 @@ struct ChunkOf {
 };
 __device__ __forceinline__ ChunkOf chunk_of(uint32_t c, uint32_t cpv, uint32_t chunk, int32_t n,
                                             const uint32_t* __restrict__ vis,
-                                            const ViewDev* __restrict__ views, int sy) {
+                                            const ViewDev* __restrict__ views,
+                                            const CellShape& s) {
   ChunkOf k;
   const uint32_t vi = c / cpv;
   k.col = c - vi * cpv;
@@ -134,19 +148,20 @@ __device__ __forceinline__ ChunkOf chunk_of(uint32_t c, uint32_t cpv, uint32_t c
   const ViewDev& v = views[vi];
   k.cell0 = (uint32_t)v.cell_off;
   k.cells_x = (uint32_t)v.cells_x;
+  const int sy = s.by - s.ay;   // tiles
   k.n_cells = k.cells_x * (((uint32_t)v.tiles_y + (1u << sy) - 1u) >> sy);
   return k;
 }
 
 __global__ __launch_bounds__(kBThreads) void cell_count_kernel(
     const uint2* __restrict__ rects, int32_t n, const uint32_t* __restrict__ vis,
-    uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per, const ViewDev* __restrict__ views, int sx, int sy,
+    uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per, const ViewDev* __restrict__ views, CellShape shape,
     uint32_t* __restrict__ counts, const Counters* __restrict__ cnt) {
   __shared__ uint32_t h[kViewCells];
   if (cnt->fail) return;
   const uint32_t c = banded_chunk(blockIdx.x, per);
   if (c >= nchunks) return;
-  const ChunkOf ck = chunk_of(c, cpv, chunk, n, vis, views, sy);
+  const ChunkOf ck = chunk_of(c, cpv, chunk, n, vis, views, shape);
   const int lane = threadIdx.x & 63;
   for (uint32_t d = threadIdx.x; d < ck.n_cells; d += kBThreads) h[d] = 0u;
   __syncthreads();
@@ -160,10 +175,11 @@ __global__ __launch_bounds__(kBThreads) void cell_count_kernel(
     }
 #pragma unroll
     for (int q = 0; q < kPerT; ++q) {
-      const CellSpan s = cell_span(r[q], sx, sy);
+      const CellSpan s = cell_span(r[q], shape);
       auto add = [&](uint2 rc, uint32_t cx, uint32_t cy) {
-        const uint32_t lr = local_rect(rc, cx, cy, sx, sy);
-        const uint32_t w = ((lr >> 3) & 7u) - (lr & 7u) + 1u, hh = (lr >> 9) - ((lr >> 6) & 7u) + 1u;
+        const LocalRect l = local_rect(rc, cx, cy, shape);
+        const uint32_t w = (l.x1 >> shape.ax) - (l.x0 >> shape.ax) + 1u;   // tiles
+        const uint32_t hh = (l.y1 >> shape.ay) - (l.y0 >> shape.ay) + 1u;
         atomicAdd(&h[cy * ck.cells_x + cx], ((w * hh) << kPairBits) | 1u);
       };
       if (s.n <= kShortRun) {
@@ -184,7 +200,7 @@ __global__ __launch_bounds__(kBThreads) void cell_count_kernel(
           return (uint32_t)__builtin_amdgcn_readlane((int)v, b);
         };
         const uint2 rc = make_uint2(from(r[q].x), from(r[q].y));
-        const CellSpan t = cell_span(rc, sx, sy);
+        const CellSpan t = cell_span(rc, shape);
         for (uint32_t k = lane; k < t.n; k += 64) {
           const uint32_t row = small_div(k, t.nx);
           add(rc, t.cx0 + (k - row * t.nx), t.cy0 + row);
@@ -274,7 +290,7 @@ template <int kSubPerT, int kWinItems>
 __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
     const uint32_t* __restrict__ sorted_slots, const uint2* __restrict__ rects, int32_t n,
     const uint32_t* __restrict__ vis, uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per,
-    const ViewDev* __restrict__ views, int sx, int sy, const uint32_t* __restrict__ counts,
+    const ViewDev* __restrict__ views, CellShape shape, const uint32_t* __restrict__ counts,
     const uint32_t* __restrict__ pair0, uint64_t capacity, uint32_t* __restrict__ pair_slot,
     uint16_t* __restrict__ pair_rect, const Counters* __restrict__ cnt) {
   constexpr int kSub = kBThreads * kSubPerT, kWin = kBThreads * kWinItems;
@@ -287,7 +303,7 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
   __shared__ uint32_t s_base[BINS];    // next free position of each cell's list
   __shared__ uint32_t s_delta[BINS];   // global minus local start of a window's run
   __shared__ uint32_t s_val[kWin];
-  __shared__ uint32_t s_pk[kWin];      // cell << 12 | rectangle within it
+  __shared__ uint32_t s_pk[kWin];      // cell << 16 | rectangle within it
   __shared__ uint32_t s_tmp[kBWaves];
   uint16_t* s_owner = reinterpret_cast<uint16_t*>(s_val);   // (dead before s_val is written)
 
@@ -295,7 +311,7 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
   if (cnt->fail || cnt->total > capacity) return;
   const uint32_t c = banded_chunk(blockIdx.x, per);
   if (c >= nchunks) return;
-  const ChunkOf ck = chunk_of(c, cpv, chunk, n, vis, views, sy);
+  const ChunkOf ck = chunk_of(c, cpv, chunk, n, vis, views, shape);
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   const int width = 32 - __clz((int)(ck.n_cells - 1u));   // bits of a cell (0: one cell)
 #pragma unroll
@@ -321,7 +337,7 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
       }
 #pragma unroll
       for (int q = 0; q < kSubPerT; ++q) {
-        nc[q] = cell_span(r[q], sx, sy).n;
+        nc[q] = cell_span(r[q], shape).n;
         sum += nc[q];
       }
       uint32_t ex = bin_block_scan(sum, s_tmp, &total);   // (also: the tables are free)
@@ -367,12 +383,12 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
         if (valid) {
           const int k = s_owner[li];
           const uint2 rc = s_rect[k];
-          const CellSpan s = cell_span(rc, sx, sy);
+          const CellSpan s = cell_span(rc, shape);
           const uint32_t l = w0 + li - s_off[k], row = small_div(l, s.nx);
           const uint32_t cx = s.cx0 + (l - row * s.nx), cy = s.cy0 + row;
           dig[r] = cy * ck.cells_x + cx;
           val[r] = s_slot[k];
-          pk[r] = (dig[r] << 12) | local_rect(rc, cx, cy, sx, sy);
+          pk[r] = (dig[r] << 16) | pack_rect(local_rect(rc, cx, cy, shape), shape);
         }
         const uint64_t m = __ballot(valid);
         lo[r] = (uint32_t)m;
@@ -436,9 +452,9 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
         const uint32_t i = r * kBThreads + t;
         if (w0 + i < w1) {
           const uint32_t p = s_pk[i];
-          const uint32_t g = s_delta[p >> 12] + i;
+          const uint32_t g = s_delta[p >> 16] + i;
           pair_slot[g] = s_val[i];
-          pair_rect[g] = (uint16_t)(p & 0xFFFu);
+          pair_rect[g] = (uint16_t)p;
         }
       }
       __syncthreads();   // the tables are rebuilt for the next window
@@ -457,31 +473,41 @@ __device__ __forceinline__ uint32_t cell_of_segment(const uint32_t* s_seg, uint3
   return __builtin_amdgcn_readfirstlane(lo);   // (sg is the same on every lane)
 }
 
-// A pair's tiles within its cell, bit (y << SX) + x.
-template <int SX, int SY>
-struct Mask {
-  static constexpr int NT = 1 << (SX + SY);
-  uint32_t lo, hi;
-  __device__ __forceinline__ bool bit(int t) const {
-    return ((t < 32 ? lo >> t : hi >> (t - 32)) & 1u) != 0;
-  }
+// The blocks of a pair's tiles: those of tile (x, y) of the cell are the bits of
+// col[x] & row[y] (row by row within the tile; 0: not covered).
+template <int SX, int SY, int AX, int AY>
+struct PairBlocks {
+  static constexpr int W = 1 << SX, H = 1 << SY, BX = SX + AX, BY = SY + AY;
+  uint32_t col[W], row[H];
+  __device__ __forceinline__ uint32_t tile(int t) const { return col[t % W] & row[t / W]; }
 };
-template <int SX, int SY>
-__device__ __forceinline__ Mask<SX, SY> tile_mask(uint32_t lr) {
-  const uint32_t x0 = lr & 7u, x1 = (lr >> 3) & 7u, y0 = (lr >> 6) & 7u, y1 = lr >> 9;
-  const uint32_t row = (2u << x1) - (1u << x0);
-  constexpr int W = 1 << SX, NT = 1 << (SX + SY);
-  uint64_t m = 0;
+template <int SX, int SY, int AX, int AY>
+__device__ __forceinline__ PairBlocks<SX, SY, AX, AY> pair_blocks(uint32_t lr, bool valid) {
+  using P = PairBlocks<SX, SY, AX, AY>;
+  constexpr int NX = 1 << AX, NY = 1 << AY;   // a tile's blocks
+  constexpr uint32_t kMX = (1u << P::BX) - 1u, kMY = (1u << P::BY) - 1u;
+  const uint32_t x0 = lr & kMX, x1 = (lr >> P::BX) & kMX;
+  const uint32_t y0 = (lr >> (2 * P::BX)) & kMY, y1 = (lr >> (2 * P::BX + P::BY)) & kMY;
+  const uint32_t xs = valid ? (uint32_t)((2ull << x1) - (1ull << x0)) : 0u;
+  const uint32_t ys = (2u << y1) - (1u << y0);
+  P b;
 #pragma unroll
-  for (int y = 0; y < (1 << SY); ++y)
-    m |= (uint32_t)y >= y0 && (uint32_t)y <= y1 ? (uint64_t)row << (W * y) : 0ull;
-  Mask<SX, SY> k;
-  k.lo = (uint32_t)m;
-  k.hi = NT > 32 ? (uint32_t)(m >> 32) : 0u;
-  return k;
+  for (int x = 0; x < P::W; ++x) {
+    const uint32_t c = (xs >> (x << AX)) & ((1u << NX) - 1u);
+    b.col[x] = NY == 2 ? c | (c << NX) : c;
+  }
+#pragma unroll
+  for (int y = 0; y < P::H; ++y) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < NY; ++k)
+      m |= (ys >> ((y << AY) + k)) & 1u ? ((1u << NX) - 1u) << (k * NX) : 0u;
+    b.row[y] = m;
+  }
+  return b;
 }
 
-template <int SX, int SY>
+template <int SX, int SY, int AX, int AY>
 __global__ __launch_bounds__(kBThreads) void seg_count_kernel(
     const uint16_t* __restrict__ pair_rect, const uint32_t* __restrict__ pair0,
     const uint32_t* __restrict__ seg0, uint32_t n_cells, uint32_t seg_shift,
@@ -509,10 +535,9 @@ __global__ __launch_bounds__(kBThreads) void seg_count_kernel(
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        Mask<SX, SY> m = tile_mask<SX, SY>(lr[q]);
-        if (p + 64 * q + lane >= end) m.lo = m.hi = 0u;
+        const auto m = pair_blocks<SX, SY, AX, AY>(lr[q], p + 64 * q + lane < end);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) n[t] += (uint32_t)__popcll(__ballot(m.bit(t)));
+        for (int t = 0; t < NT; ++t) n[t] += (uint32_t)__popcll(__ballot(m.tile(t) != 0u));
       }
     }
     uint32_t mine = 0;
@@ -583,12 +608,12 @@ __global__ __launch_bounds__(kBThreads) void cell_tiles_kernel(
   }
 }
 
-template <int SX, int SY>
+template <int SX, int SY, int AX, int AY>
 __global__ __launch_bounds__(kBThreads) void seg_emit_kernel(
     const uint32_t* __restrict__ pair_slot, const uint16_t* __restrict__ pair_rect,
     const uint32_t* __restrict__ pair0, const uint32_t* __restrict__ seg0, uint32_t n_cells,
-    uint32_t seg_shift, const uint32_t* __restrict__ segs, uint32_t* __restrict__ list,
-    const Counters* __restrict__ cnt) {
+    uint32_t seg_shift, const uint32_t* __restrict__ segs, uint32_t pack_mask,
+    uint32_t* __restrict__ list, const Counters* __restrict__ cnt) {
   constexpr int NT = 1 << (SX + SY);
   __shared__ uint32_t s_seg[kMaxCells + 1];
   if (cnt->fail) return;
@@ -613,21 +638,21 @@ __global__ __launch_bounds__(kBThreads) void seg_emit_kernel(
     }
     for (uint32_t p = first; p < end; p += 64) {
       const uint32_t slot = slot_n;
-      Mask<SX, SY> m = tile_mask<SX, SY>(lr_n);
-      if (p + lane >= end) m.lo = m.hi = 0u;
+      const auto m = pair_blocks<SX, SY, AX, AY>(lr_n, p + lane < end);
       if (p + 64 + lane < end) {   // (the next 64 pairs' reads in flight meanwhile)
         slot_n = pair_slot[p + 64 + lane];
         lr_n = pair_rect[p + 64 + lane];
       }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const bool in = m.bit(t);
+        const uint32_t blocks = m.tile(t);
+        const bool in = blocks != 0u;
         const uint64_t who = __ballot(in);
         if (who) {
           if (in)
             list[__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
                                            __builtin_amdgcn_mbcnt_lo((uint32_t)who, at[t]))] =
-                slot;
+                slot | ((blocks << 28) & pack_mask);
           at[t] += (uint32_t)__popcll(who);
         }
       }
@@ -640,11 +665,15 @@ __global__ __launch_bounds__(kBThreads) void seg_emit_kernel(
 // The smallest cells of which no view has more than kViewCells and the render
 // no more than kMaxCells: smaller cells mean more pairs per slot but fewer
 // tiles to test per pair.
-BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, int32_t n) {
+BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, int32_t n,
+                  int tile_w, int tile_h) {
   const int shapes[3][2] = {{2, 2}, {3, 2}, {3, 3}};
   BinPlan p{};
   p.n = n;
   p.n_views = n_views;
+  p.ax = tile_w == 32 ? 2 : tile_w == 16 ? 1 : 0;
+  p.ay = tile_h == 16 ? 1 : 0;
+  p.pack = (int64_t)n * n_views <= kPackedSlots;
   for (int k = 0; k < 3 && n_views <= kMaxBinViews && !p.n_cells; ++k) {
     p.sx = shapes[k][0];
     p.sy = shapes[k][1];
@@ -683,6 +712,8 @@ size_t bin_seg_words(const BinPlan& p, uint64_t max_pairs) {
 
 namespace {
 
+CellShape shape_of(const BinPlan& p) { return {p.sx + p.ax, p.sy + p.ay, p.ax, p.ay}; }
+
 struct CellArrays {
   uint32_t *totals, *weights, *pair0, *seg0, *inst0;
 };
@@ -691,20 +722,31 @@ CellArrays cell_arrays(const BinPlan& p, const BinBuffers& b) {
   return {b.cells, b.cells + k, b.cells + 2 * k, b.cells + 3 * k + 1, b.cells + 4 * k + 2};
 }
 
-template <int SX, int SY>
+template <int SX, int SY, int AX, int AY>
 void fine_t(const BinPlan& p, const BinBuffers& b, uint64_t m_plan, const ViewDev* views,
             const Counters* counters, hipStream_t s) {
   const CellArrays a = cell_arrays(p, b);
   // a wave per segment, looping beyond the grid
   const uint64_t segs = (m_plan >> p.seg_shift) + p.n_cells;
   const unsigned grid = (unsigned)std::min<uint64_t>((segs + kBWaves - 1) / kBWaves, kMaxFineGrid);
-  hipLaunchKernelGGL((seg_count_kernel<SX, SY>), dim3(grid), dim3(kBThreads), 0, s, b.pair_rect,
+  hipLaunchKernelGGL((seg_count_kernel<SX, SY, AX, AY>), dim3(grid), dim3(kBThreads), 0, s, b.pair_rect,
                      a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs, counters);
   hipLaunchKernelGGL((cell_tiles_kernel<SX, SY>), dim3(p.n_cells), dim3(kBThreads), 0, s, views,
                      p.n_views, a.seg0, a.inst0, b.segs, b.ranges, counters);
-  hipLaunchKernelGGL((seg_emit_kernel<SX, SY>), dim3(grid), dim3(kBThreads), 0, s, b.pair_slot,
-                     b.pair_rect, a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs, b.list,
-                     counters);
+  hipLaunchKernelGGL((seg_emit_kernel<SX, SY, AX, AY>), dim3(grid), dim3(kBThreads), 0, s, b.pair_slot,
+                     b.pair_rect, a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs,
+                     p.pack ? ~kPackMask : 0u, b.list, counters);
+}
+
+template <int AX, int AY>
+void fine_a(const BinPlan& p, const BinBuffers& b, uint64_t m_plan, const ViewDev* views,
+            const Counters* counters, hipStream_t s) {
+  if (p.sx == 2)
+    fine_t<2, 2, AX, AY>(p, b, m_plan, views, counters, s);
+  else if (p.sy == 2)
+    fine_t<3, 2, AX, AY>(p, b, m_plan, views, counters, s);
+  else
+    fine_t<3, 3, AX, AY>(p, b, m_plan, views, counters, s);
 }
 
 }  // namespace
@@ -716,7 +758,7 @@ void launch_bin_count(const BinPlan& p, const BinBuffers& b, const uint2* rects,
   const CellArrays a = cell_arrays(p, b);
   const uint32_t nchunks = p.cpv * p.n_views, per = (nchunks + kXcds - 1) / kXcds;
   hipLaunchKernelGGL(cell_count_kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, rects, p.n, vis,
-                     nchunks, p.cpv, (uint32_t)p.chunk, per, views, p.sx, p.sy, b.counts,
+                     nchunks, p.cpv, (uint32_t)p.chunk, per, views, shape_of(p), b.counts,
                      counters);
   hipLaunchKernelGGL(cell_scan_kernel, dim3(p.n_cells), dim3(kBThreads), 0, s, b.counts, p.cpv,
                      a.totals, a.weights, counters);
@@ -732,7 +774,7 @@ void launch_bin_scatter(const BinPlan& p, const BinBuffers& b, const uint32_t* s
   const uint32_t nchunks = p.cpv * p.n_views, per = (nchunks + kXcds - 1) / kXcds;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, sorted_slots, rects, p.n, vis,
-                       nchunks, p.cpv, (uint32_t)p.chunk, per, views, p.sx, p.sy, b.counts,
+                       nchunks, p.cpv, (uint32_t)p.chunk, per, views, shape_of(p), b.counts,
                        a.pair0, capacity, b.pair_slot, b.pair_rect, counters);
   };
   if (p.chunk >= 512)
@@ -744,12 +786,12 @@ void launch_bin_scatter(const BinPlan& p, const BinBuffers& b, const uint32_t* s
 void launch_bin_tiles(const BinPlan& p, const BinBuffers& b, uint64_t m_plan,
                       const ViewDev* views, const Counters* counters, hipStream_t s) {
   if (p.n <= 0) return;
-  if (p.sx == 2)
-    fine_t<2, 2>(p, b, m_plan, views, counters, s);
-  else if (p.sy == 2)
-    fine_t<3, 2>(p, b, m_plan, views, counters, s);
+  if (p.ax == 0)
+    fine_a<0, 0>(p, b, m_plan, views, counters, s);
+  else if (p.ax == 1)
+    fine_a<1, 1>(p, b, m_plan, views, counters, s);
   else
-    fine_t<3, 3>(p, b, m_plan, views, counters, s);
+    fine_a<2, 0>(p, b, m_plan, views, counters, s);
 }
 
 }  // namespace nxs

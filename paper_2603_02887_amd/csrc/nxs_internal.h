@@ -41,8 +41,9 @@ struct GaussDev {
 // Per projected slot (slot = view * n + gaussian) arrays written by the projection.
 struct ProjDev {
   uint32_t* depth_key;      // float32 depth bits; 0xFFFFFFFF when culled
-  // tile rectangle (tx0 | tx1 << 16, ty0 | ty1 << 16), all ones when culled;
-  // the covered tiles are rect_tile_count(trect[slot])
+  // rectangle (x0 | x1 << 16, y0 | y1 << 16), all ones when culled: in blocks
+  // of 8x8 pixels for the two-level binning (the tiles it covers are
+  // tile_rect() of it), else in tiles
   uint2* trect;
   // 3 float4 per slot:
   //   (u_hi, u_lo, v_hi, v_lo)  image-plane centre as float hi + lo parts
@@ -160,6 +161,14 @@ __device__ __forceinline__ uint32_t lanes_below(uint32_t lo, uint32_t hi) {
   return __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
 }
 
+// A rectangle of 8x8 blocks in tiles of 2^ax x 2^ay blocks (culled: stays so).
+__host__ __device__ __forceinline__ uint2 tile_rect(uint2 r, int ax, int ay) {
+  if (r.x == 0xFFFFFFFFu) return r;
+  r.x = ((r.x & 0xFFFFu) >> ax) | ((r.x >> 16 >> ax) << 16);
+  r.y = ((r.y & 0xFFFFu) >> ay) | ((r.y >> 16 >> ay) << 16);
+  return r;
+}
+
 // The tiles a slot's rectangle covers (0 for a culled slot).
 __device__ __forceinline__ uint32_t rect_tile_count(uint2 r) {
   if (r.x == 0xFFFFFFFFu) return 0u;
@@ -187,10 +196,11 @@ struct ViewArgs {
 // kArgViews views (host memory, read during the call), which the projection
 // writes to `views`; otherwise `views` must already hold them.  Returns
 // false if host_views was given but cannot be used (no Gaussians): the
-// caller then copies the table itself.
+// caller then copies the table itself.  The rectangles are in units of
+// 2^unit_x x 2^unit_y pixels, a tile 2^ax x 2^ay units.
 size_t project_partials_size(int n);
 bool launch_project(const GaussDev& g, ViewDev* views, const ViewDev* host_views, int n_views,
-                    float kappa2, float alpha_min, int tile_w, int tile_h,
+                    float kappa2, float alpha_min, int unit_x, int unit_y, int ax, int ay,
                     const ProjDev& out, uint4* partials, Counters* counters,
                     const DeferCheck& check, uint32_t* clear, int64_t n_clear,
                     hipStream_t s);
@@ -251,8 +261,16 @@ constexpr int kMaxBinViews = 64;
 constexpr int kMaxCellTiles = 64;     // a pair's tiles are one bit each
 constexpr int kMaxCellChunk = 4096;   // slots counted together
 constexpr int kMaxFineGrid = 4096;    // work-groups of the per-segment kernels
+//
+// With `pack` a list entry's four top bits say which of the tile's 8x8 blocks
+// (at most 4, row by row) the slot's rectangle covers, below them the slot
+// (kPackedSlots at most); without, it is the slot alone.
+constexpr uint32_t kPackMask = 0x0FFFFFFFu;
+constexpr int64_t kPackedSlots = int64_t(1) << 28;
 struct BinPlan {
   int sx, sy;         // log2 of a cell's tiles per row and column
+  int ax, ay;         // log2 of a tile's 8x8 blocks per row and column
+  bool pack;
   uint32_t n_cells;   // 0: the two-level binning does not apply
   int32_t n;          // slots per view
   int n_views;
@@ -269,7 +287,8 @@ struct BinBuffers {
   uint32_t* list;        // one entry per instance
   uint2* ranges;         // per tile; those without instances are left as they are
 };
-BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, int32_t n);
+BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, int32_t n,
+                  int tile_w, int tile_h);
 size_t bin_counts_words(const BinPlan& p);
 size_t bin_cells_words(const BinPlan& p);
 size_t bin_seg_words(const BinPlan& p, uint64_t max_pairs);
@@ -310,10 +329,11 @@ void launch_emit_write(const uint32_t* sorted_slots, const uint2* rect_sorted,
 // float32 depth bits (depth_key), in LDS up to kSegMax entries and through
 // `temp` (the same positions) beyond; the bits that vary come from the
 // projection's counters.  Nothing is done for a failed deferred render.
+// (slot_mask: the bits of an entry that are its slot)
 constexpr int kSegMax = 4096;
 void launch_tile_depth_sort(const uint2* ranges, int64_t n_tiles, const uint32_t* depth_key,
-                            const Counters* counters, uint32_t* list, uint32_t* temp,
-                            hipStream_t s);
+                            const Counters* counters, uint32_t slot_mask, uint32_t* list,
+                            uint32_t* temp, hipStream_t s);
 
 
 
@@ -334,6 +354,8 @@ struct CompositeParams {
   float param;              // operator parameter (c, gamma or v) for models 4..7
   float bg[3];
   int32_t lds_batch;        // list entries gathered per round: 64, 128 or 256
+  // list entries: kPackMask (slot, and the blocks it covers above it) or ~0
+  uint32_t slot_mask;
 };
 // pstate: null, or 3 float4 per pixel kept for the backward pass:
 //   (L0, L1, L2, T_final), (E_k, tau_k), (U, 0) with E_k the saturating splat's

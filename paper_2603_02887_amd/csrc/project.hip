@@ -36,8 +36,8 @@ struct KeyGeom {
 __device__ __forceinline__ KeyGeom key_recipe(const float* m, const float* s,
                                               const float* q, float aleph,
                                               const ViewDev& v, float kappa2,
-                                              float alpha_min, int tile_w,
-                                              int tile_h) {
+                                              float alpha_min, int unit_x,
+                                              int unit_y) {
 #pragma clang fp contract(off)
   KeyGeom out;
   out.visible = false;
@@ -105,10 +105,10 @@ __device__ __forceinline__ KeyGeom key_recipe(const float* m, const float* s,
   if (!(x0 <= x1) || !(y0 <= y1)) return out;
   out.visible = true;
   out.depth_bits = __float_as_uint(pz);
-  out.tx0 = (int)x0 / tile_w;
-  out.tx1 = (int)x1 / tile_w;
-  out.ty0 = (int)y0 / tile_h;
-  out.ty1 = (int)y1 / tile_h;
+  out.tx0 = (int)x0 >> unit_x;   // (x0, y0 >= 0)
+  out.tx1 = (int)x1 >> unit_x;
+  out.ty0 = (int)y0 >> unit_y;
+  out.ty1 = (int)y1 >> unit_y;
   return out;
 }
 
@@ -267,7 +267,7 @@ __device__ void fold_partials(const uint4* partials, int nblocks, Counters* c,
 template <int DEG, bool ARGS>
 __global__ __launch_bounds__(kBlock) void project_kernel(
     GaussDev g, ViewDev* __restrict__ views, ViewArgs va, int n_views, float kappa2,
-    float alpha_min, int tile_w, int tile_h, ProjDev out, uint4* __restrict__ partials,
+    float alpha_min, int unit_x, int unit_y, int ax, int ay, ProjDev out, uint4* __restrict__ partials,
     uint32_t* __restrict__ clear, int64_t n_clear) {
   constexpr int K = (DEG + 1) * (DEG + 1);
   if (ARGS && blockIdx.x == 0) {
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kBlock) void project_kernel(
     if (!valid) break;
     const ViewDev& v = ARGS ? va.v[vi] : views[vi];
     const int64_t slot = (int64_t)vi * g.n + i;
-    KeyGeom kg = key_recipe(m, s, q, aleph, v, kappa2, alpha_min, tile_w, tile_h);
+    KeyGeom kg = key_recipe(m, s, q, aleph, v, kappa2, alpha_min, unit_x, unit_y);
     uint2 rect = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
     uint32_t nt = 0;
     if (kg.visible) {
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kBlock) void project_kernel(
       dmax = max(dmax, kg.depth_bits);
       rect = make_uint2((uint32_t)kg.tx0 | ((uint32_t)kg.tx1 << 16),
                         (uint32_t)kg.ty0 | ((uint32_t)kg.ty1 << 16));
-      nt = rect_tile_count(rect);
+      nt = rect_tile_count(tile_rect(rect, ax, ay));
       // ---- composite footprint ----------------------------------------------
       // Sigma2D = A A^T + 0.3 I from the recipe's A (float32).  Its determinant
       // by Cauchy-Binet, |A0 x A1|^2 + 0.3 (|A0|^2 + |A1|^2) + 0.09, is a sum
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kFoldThreads) void reduce_counters_kernel(
 }  // namespace
 
 bool launch_project(const GaussDev& g, ViewDev* views, const ViewDev* host_views, int n_views,
-                    float kappa2, float alpha_min, int tile_w, int tile_h,
+                    float kappa2, float alpha_min, int unit_x, int unit_y, int ax, int ay,
                     const ProjDev& out, uint4* partials, Counters* counters,
                     const DeferCheck& check, uint32_t* clear, int64_t n_clear,
                     hipStream_t s) {
@@ -498,11 +498,11 @@ bool launch_project(const GaussDev& g, ViewDev* views, const ViewDev* host_views
 #define NXS_PROJECT(D)                                                                     \
   if (args)                                                                                \
     hipLaunchKernelGGL((project_kernel<D, true>), dim3(nblocks), dim3(kBlock), 0, s, g,    \
-                       views, va, n_views, kappa2, alpha_min, tile_w, tile_h, out,         \
+                       views, va, n_views, kappa2, alpha_min, unit_x, unit_y, ax, ay, out, \
                        partials, clear, n_clear);                                          \
   else                                                                                     \
     hipLaunchKernelGGL((project_kernel<D, false>), dim3(nblocks), dim3(kBlock), 0, s, g,   \
-                       views, va, n_views, kappa2, alpha_min, tile_w, tile_h, out,         \
+                       views, va, n_views, kappa2, alpha_min, unit_x, unit_y, ax, ay, out, \
                        partials, clear, n_clear)
   if (any) {
     switch (g.sh_degree) {

@@ -386,8 +386,8 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
 
 // ------------------------------------------------- per-tile depth sort
 
-// One work-group sorts one tile's list (slots in slot order after the stable
-// tile sort) stably by the slots' depth bits: LSD passes of balanced digits
+// One work-group sorts one tile's list (entries in slot order, the slot their
+// bits in `sm`) stably by the slots' depth bits: LSD passes of balanced digits
 // of up to kMaxDigitBits over the bits that vary among visible depths, each
 // pass ranked like a scatter chunk (wave ballots, per-wave digit counters,
 // a scan over the digits, two per thread).  Up to kSegMax entries live in
@@ -465,7 +465,7 @@ struct SegLds {
 // All passes in LDS (m <= 256 * ITEMS <= kSegMax).
 template <int ITEMS>
 __device__ void seg_sort_lds(uint32_t* list, int m, const uint32_t* __restrict__ depth_key,
-                             const int* shifts, const int* widths, int passes, SegLds& L) {
+                             uint32_t sm, const int* shifts, const int* widths, int passes, SegLds& L) {
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   uint32_t k[ITEMS], v[ITEMS];
 #pragma unroll
@@ -476,7 +476,7 @@ __device__ void seg_sort_lds(uint32_t* list, int m, const uint32_t* __restrict__
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     const int li = wid * (64 * ITEMS) + r * 64 + lane;
-    k[r] = li < m ? depth_key[v[r]] : 0u;
+    k[r] = li < m ? depth_key[v[r] & sm] : 0u;
   }
   for (int p = 0; p < passes; ++p) {
     for (int i = t; i < kRWaves * kRBins; i += kRThreads) (&L.wave[0][0])[i] = 0u;
@@ -515,8 +515,8 @@ __device__ void seg_sort_lds(uint32_t* list, int m, const uint32_t* __restrict__
 // A list longer than kSegMax: every pass counts the whole list, then ranks
 // and writes it chunk by chunk in order, between `list` and `temp`.
 __device__ void seg_sort_global(uint32_t* list, uint32_t* temp, int m,
-                                const uint32_t* __restrict__ depth_key, const int* shifts,
-                                const int* widths, int passes, SegLds& L) {
+                                const uint32_t* __restrict__ depth_key, uint32_t sm,
+                                const int* shifts, const int* widths, int passes, SegLds& L) {
   constexpr int ITEMS = kSegMax / kRThreads;
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   uint32_t* src = list;
@@ -527,7 +527,7 @@ __device__ void seg_sort_global(uint32_t* list, uint32_t* temp, int m,
     for (int i = t; i < kRBins; i += kRThreads) L.run[i] = 0u;
     __syncthreads();
     for (int i = t; i < m; i += kRThreads)
-      atomicAdd(&L.run[(depth_key[src[i]] >> shift) & mask], 1u);
+      atomicAdd(&L.run[(depth_key[src[i] & sm] >> shift) & mask], 1u);
     __syncthreads();
     {
       // exclusive scan of the digit totals: the first position of each digit
@@ -550,7 +550,7 @@ __device__ void seg_sort_global(uint32_t* list, uint32_t* temp, int m,
 #pragma unroll
       for (int r = 0; r < ITEMS; ++r) {
         const int li = wid * (64 * ITEMS) + r * 64 + lane;
-        k[r] = li < cm ? depth_key[v[r]] : 0u;
+        k[r] = li < cm ? depth_key[v[r] & sm] : 0u;
       }
       for (int i = t; i < kRWaves * kRBins; i += kRThreads) (&L.wave[0][0])[i] = 0u;
       __syncthreads();
@@ -600,7 +600,7 @@ struct SegWaveLds {
 
 template <int ITEMS>
 __device__ void seg_sort_wave(uint32_t* list, int m, const uint32_t* __restrict__ depth_key,
-                              const int* shifts, const int* widths, int passes,
+                              uint32_t sm, const int* shifts, const int* widths, int passes,
                               SegWaveLds& L) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
@@ -608,7 +608,7 @@ __device__ void seg_sort_wave(uint32_t* list, int m, const uint32_t* __restrict_
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) v[r] = r * 64 + lane < m ? list[r * 64 + lane] : 0u;
 #pragma unroll
-  for (int r = 0; r < ITEMS; ++r) k[r] = r * 64 + lane < m ? depth_key[v[r]] : 0u;
+  for (int r = 0; r < ITEMS; ++r) k[r] = r * 64 + lane < m ? depth_key[v[r] & sm] : 0u;
   for (int p = 0; p < passes; ++p) {
     const int shift = shifts[p], width = widths[p], nd = 1 << width;
     const uint32_t mask = (1u << width) - 1u;
@@ -692,7 +692,7 @@ __device__ __forceinline__ int seg_plan(const Counters* __restrict__ cnt, int* s
 // for tile_depth_sort_kernel).
 __global__ __launch_bounds__(64) void tile_depth_sort_wave_kernel(
     const uint2* __restrict__ ranges, uint32_t n_tiles, const uint32_t* __restrict__ depth_key,
-    const Counters* __restrict__ cnt, uint32_t* __restrict__ list) {
+    const Counters* __restrict__ cnt, uint32_t sm, uint32_t* __restrict__ list) {
   __shared__ SegWaveLds L;
   const uint32_t tile = blockIdx.x;
   if (tile >= n_tiles || cnt->fail) return;
@@ -704,20 +704,21 @@ __global__ __launch_bounds__(64) void tile_depth_sort_wave_kernel(
   if (passes == 0) return;   // equal depths: slot order is the order
   uint32_t* seg = list + rg.x;
   if (m <= 64)
-    seg_sort_wave<1>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_wave<1>(seg, m, depth_key, sm, shifts, widths, passes, L);
   else if (m <= 128)
-    seg_sort_wave<2>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_wave<2>(seg, m, depth_key, sm, shifts, widths, passes, L);
   else if (m <= 256)
-    seg_sort_wave<4>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_wave<4>(seg, m, depth_key, sm, shifts, widths, passes, L);
   else if (m <= 512)
-    seg_sort_wave<8>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_wave<8>(seg, m, depth_key, sm, shifts, widths, passes, L);
   else
-    seg_sort_wave<16>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_wave<16>(seg, m, depth_key, sm, shifts, widths, passes, L);
 }
 
 __global__ __launch_bounds__(kRThreads) void tile_depth_sort_kernel(
     const uint2* __restrict__ ranges, uint32_t n_tiles, const uint32_t* __restrict__ depth_key,
-    const Counters* __restrict__ cnt, uint32_t* __restrict__ list, uint32_t* __restrict__ temp) {
+    const Counters* __restrict__ cnt, uint32_t sm, uint32_t* __restrict__ list,
+    uint32_t* __restrict__ temp) {
   __shared__ SegLds L;
   const uint32_t tile = blockIdx.x;
   if (tile >= n_tiles || cnt->fail) return;
@@ -729,11 +730,11 @@ __global__ __launch_bounds__(kRThreads) void tile_depth_sort_kernel(
   if (passes == 0) return;   // equal depths: slot order is the order
   uint32_t* seg = list + rg.x;
   if (m <= 2048)
-    seg_sort_lds<8>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_lds<8>(seg, m, depth_key, sm, shifts, widths, passes, L);
   else if (m <= kSegMax)
-    seg_sort_lds<16>(seg, m, depth_key, shifts, widths, passes, L);
+    seg_sort_lds<16>(seg, m, depth_key, sm, shifts, widths, passes, L);
   else
-    seg_sort_global(seg, temp + rg.x, m, depth_key, shifts, widths, passes, L);
+    seg_sort_global(seg, temp + rg.x, m, depth_key, sm, shifts, widths, passes, L);
 }
 
 }  // namespace
@@ -823,13 +824,13 @@ int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
 }
 
 void launch_tile_depth_sort(const uint2* ranges, int64_t n_tiles, const uint32_t* depth_key,
-                            const Counters* counters, uint32_t* list, uint32_t* temp,
-                            hipStream_t s) {
+                            const Counters* counters, uint32_t slot_mask, uint32_t* list,
+                            uint32_t* temp, hipStream_t s) {
   if (n_tiles <= 0) return;
   hipLaunchKernelGGL(tile_depth_sort_wave_kernel, dim3((unsigned)n_tiles), dim3(64), 0, s,
-                     ranges, (uint32_t)n_tiles, depth_key, counters, list);
+                     ranges, (uint32_t)n_tiles, depth_key, counters, slot_mask, list);
   hipLaunchKernelGGL(tile_depth_sort_kernel, dim3((unsigned)n_tiles), dim3(kRThreads), 0, s,
-                     ranges, (uint32_t)n_tiles, depth_key, counters, list, temp);
+                     ranges, (uint32_t)n_tiles, depth_key, counters, slot_mask, list, temp);
 }
 
 }  // namespace nxs
