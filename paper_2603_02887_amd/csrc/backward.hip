@@ -119,13 +119,17 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
     s1 = st[1];
     s2 = st[2];
   }
-  // exponential: radiance not yet attributed, 4 channels (rgb, T)
-  float R0 = s0.x, R1 = s0.y, R2 = s0.z, R3 = s0.w;
-  // linear / quadratic: E_k (4 channels) and Theta (4 channels)
-  const bool saturated = s0.w == 0.0f;
-  const float k0 = s1.x, k1 = s1.y, k2 = s1.z, k3 = saturated ? 0.0f : 1.0f;
-  float th0 = s2.x - k0 * s1.w, th1 = s2.y - k1 * s1.w, th2 = s2.z - k2 * s1.w,
-        th3 = -k3 * s1.w;
+  // Only the projections of the channels on the upstream gradient are needed
+  // (g . x over rgb and T, whose emission is 0 and background 1), so one
+  // number per pixel replaces four:
+  // exponential: g . the radiance not yet attributed, and g . L_b
+  float Rg = g0 * s0.x + g1 * s0.y + g2 * s0.z + gT * s0.w;
+  const float bgg = g0 * prm.bg[0] + g1 * prm.bg[1] + g2 * prm.bg[2] + gT;
+  // linear / quadratic: g . E_k and g . Theta
+  const float k3 = s0.w == 0.0f ? 0.0f : 1.0f;   // (saturated: 0)
+  const float kg = g0 * s1.x + g1 * s1.y + g2 * s1.z + gT * k3;
+  float thg = g0 * (s2.x - s1.x * s1.w) + g1 * (s2.y - s1.y * s1.w) +
+              g2 * (s2.z - s1.z * s1.w) - gT * (k3 * s1.w);
 
   Op<MODEL> op;
   bool done = !inside;
@@ -172,33 +176,19 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
       const float T_before = op.T, tau_before = op.tau;
       bool stops;
       const float p = op.step(a, param, t_eps, stops);
-      float dalpha = 0.0f;
+      float dalpha;
+      bool adds = contrib;
       if (MODEL == 0) {
-        R0 -= r[6] * p;
-        R1 -= r[7] * p;
-        R2 -= r[8] * p;
-      }
-      if (contrib) {
-        if (MODEL == 0) {
-          if (stops) {
-            dalpha = T_before * (g0 * (r[6] - prm.bg[0]) + g1 * (r[7] - prm.bg[1]) +
-                                 g2 * (r[8] - prm.bg[2]) - gT);
-          } else {
-            // (1 - a > 0 here: a splat with a = 1 leaves T = 0 and stops the pixel)
-            const float inv = __builtin_amdgcn_rcpf(1.0f - a);
-            dalpha = T_before * (g0 * r[6] + g1 * r[7] + g2 * r[8]) -
-                     inv * (g0 * R0 + g1 * R1 + g2 * R2 + gT * R3);
-          }
-        } else if (!stops) {   // the saturating splat takes the remainder: 0
-          const float e0 = r[6] - k0, e1 = r[7] - k1, e2 = r[8] - k2, e3 = -k3;
-          th0 -= e0 * a;
-          th1 -= e1 * a;
-          th2 -= e2 * a;
-          th3 -= e3 * a;
-          const float w = fmaf(c, tau_before, 1.0f);
-          dalpha = g0 * fmaf(e0, w, c * th0) + g1 * fmaf(e1, w, c * th1) +
-                   g2 * fmaf(e2, w, c * th2) + gT * fmaf(e3, w, c * th3);
-        }
+        const float G = fmaf(g0, r[6], fmaf(g1, r[7], g2 * r[8]));   // g . E
+        Rg = fmaf(-G, p, Rg);
+        // (1 - a > 0 unless the splat stops the pixel: one with a = 1 leaves T = 0)
+        const float behind = stops ? T_before * bgg : __builtin_amdgcn_rcpf(1.0f - a) * Rg;
+        dalpha = fmaf(T_before, G, -behind);
+      } else {
+        const float G = fmaf(g0, r[6], fmaf(g1, r[7], fmaf(g2, r[8], -kg)));   // g . (E - E_k)
+        thg = fmaf(-G, a, thg);
+        dalpha = fmaf(G, fmaf(c, tau_before, 1.0f), c * thg);
+        adds = contrib && !stops;   // the saturating splat takes the remainder: 0
       }
       done = done || stops;
       // alpha = aleph exp(-q/2), q = A dx^2 + 2 B dx dy + C dy^2: with
@@ -207,7 +197,7 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
       // dL/d(A, B, C) = -da (dx^2 / 2, dx dy, dy^2 / 2), all linear in the
       // moments da (1, dx, dy, dx^2, dx dy, dy^2): the wave sums those, and
       // project_bwd applies the slot's aleph and conic once per slot
-      const float da = dalpha * a;
+      const float da = adds ? dalpha * a : 0.0f;
       const float dax = da * dx, day = da * dy;
       if (__builtin_amdgcn_ballot_w64(contrib) != 0) {
         float t[9] = {quad_total(da),       quad_total(dax),      quad_total(day),
