@@ -35,30 +35,33 @@ namespace {
 constexpr float kL2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;   // 1 / log2(e)
 
-// Sum over each row of 16 lanes with DPP adds (VALU only): pairs and quads
-// by quad_perm, then half-rows and rows by mirror patterns; every lane of a
-// row ends with the row's total.
+// x + the y of another lane of the row of 16 (CTRL; 0 where there is none).
 // (no contraction: an add of the moved value folds into one DPP add, which a
 // product of the caller fused into an FMA with it would prevent)
 template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x) {
+__device__ __forceinline__ float dpp_add(float x, float y) {
 #pragma clang fp contract(off)
-  const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true);
-  return x + __int_as_float(y);
+  const int m = __builtin_amdgcn_update_dpp(0, __float_as_int(y), CTRL, 0xF, 0xF, true);
+  return x + __int_as_float(m);
 }
-__device__ __forceinline__ float quad_total(float x) {
-  x = dpp_add<0xB1>(x);    // quad_perm [1,0,3,2]
-  x = dpp_add<0x4E>(x);    // quad_perm [2,3,0,1]
-  return x;
-}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor8 = 0x128;   // quad_perm, quad_perm, row_ror:8
+constexpr int kFrom4 = 0x104;                              // row_shl:4, lane j reads j + 4
+constexpr int kRor4 = 0x124;                               // row_ror:4
 
-// Per-wave sums of the 9 per-pixel fields of up to kRedSplats splats at a
-// time: each splat's fields are summed over lane quads (two DPP adds each)
-// and the quads' first lanes write the 16 quad sums of field f to row
-// 9 j + f of the wave's table (j: the splat's place among the pending ones);
-// a flush has lane r add row r's 16 sums and issue its atomic.
-constexpr int kRedSplats = 4;                    // 36 rows: one per lane
-constexpr int kRedF4 = 9 * kRedSplats * 16 / 4;  // float4 per wave
+// Per-wave sums over the 64 pixels of the 9 fields da (1, dx, dy, dx^2, dx dy,
+// dy^2) and p g_rgb.  Of each contributing splat every lane leaves only da and p
+// in two rows of the wave's table; a flush gives each of the kRedSplats pending
+// splats a row of 16 lanes, a lane four pixels of one image row, over which it
+// forms the sums in registers (dy is one number for them), and folds the 16
+// lanes, each fold halving the fields that a lane still carries.  The kernel is
+// bound by VALU issue (88% busy): this takes about 18 instructions a splat,
+// where forming nine products in every lane and adding them over lane quads
+// took 32 and nine LDS writes (8 views of 720p, 500k splats: 910 -> 770 us;
+// 1080p, 1M, quadratic: 132 -> 115 us).  Eight splats a flush need fewer
+// instructions but 4 KB more LDS a work-group, and lose to it (1013 us at five
+// waves a SIMD).  The table is sized so that eight work-groups fit a CU's LDS.
+constexpr int kRedSplats = 4;
+constexpr int kRedF4 = 2 * kRedSplats * 64 / 4;  // float4 per wave
 
 template <int MODEL, int TW, int TH>
 __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
@@ -67,8 +70,7 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
     const float4* __restrict__ pstate, float* __restrict__ gslot, uint32_t n_tiles,
     uint32_t per_xcd, const uint32_t* __restrict__ order) {
   __shared__ float4 stage[(TW / 8) * (TH / 8) * kStageF4];
-  __shared__ float4 rsum[(TW / 8) * (TH / 8) * kRedF4];   // per wave: pending quad sums
-  __shared__ uint32_t rslot[(TW / 8) * (TH / 8) * kRedSplats];   // and their slots
+  __shared__ float4 rsum[(TW / 8) * (TH / 8) * kRedF4];   // per wave: pending da and p
   // the forward's order (longest tile lists first) when it made one, else
   // each XCD a contiguous band of tiles
   const uint32_t w = order ? blockIdx.x : xcd_banded(blockIdx.x, per_xcd);
@@ -96,7 +98,6 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
   const StageBlock sb = stage_block<TW>(tx, ty, TH, wid, prm.log2_alpha_min);
   float4* wlds = stage + wid * kStageF4;
   float* wred = reinterpret_cast<float*>(rsum + wid * kRedF4);
-  uint32_t* wslot = rslot + wid * kRedSplats;
   const uint2 rg = ranges[tile];
   const float amin = prm.log2_alpha_min;
   const float t_eps = prm.t_eps;
@@ -132,10 +133,9 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
               g2 * (s2.z - s1.z * s1.w) - gT * (k3 * s1.w);
 
   Op<MODEL> op;
-  bool done = !inside;
   // running lanes; each batch is staged against the rows and columns that
   // still hold one
-  uint64_t act = __builtin_amdgcn_ballot_w64(!done);
+  uint64_t act = __builtin_amdgcn_ballot_w64(inside);
   // (an empty tile fetches nothing: its range is [0, 0) or [x, x))
   StageSlot slots{0u, false};
   StageFetch fetched{};
@@ -144,38 +144,87 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
     fetched = stage_records(slots, rec, prm.slot_mask, wid);
     slots = stage_slot(inst_val, (uint64_t)rg.x + 64, rg.y, lane);
   }
-  // the pending splats' sums: lane r < 9 pend adds row r and issues its atomic
-  uint32_t pend = 0;
+  // The flush's view of the block: lane 16 s + j has splat s and pixels 4 j .. 4 j
+  // + 3, that is columns 4 (j & 1) + 0 .. 3 of row j >> 1, and their g_rgb.
+  const int fs = lane >> 4, fj = lane & 15;
+  const float fcx = (float)(bx + 4 * (fj & 1)) + 0.5f, fcy = (float)(by + (fj >> 1)) + 0.5f;
+  float4 h0, h1, h2;
+  {
+    wred[lane] = g0;
+    wred[64 + lane] = g1;
+    wred[128 + lane] = g2;
+    wave_lds_order();
+    const float4* q = reinterpret_cast<const float4*>(wred) + fj;
+    h0 = q[0];
+    h1 = q[16];
+    h2 = q[32];
+    wave_lds_order();
+  }
+  // the field that lane j of a row ends with (below), 9: none
+  const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0, b3 = (lane & 8) != 0;
+  const int field = (lane & 4) == 0 ? (b0 ? 4 : 0) + (b1 ? 2 : 0) + (b3 ? 1 : 0)
+                                    : fj == 4 ? 8 : 9;
+  float fu = 0.0f, fv = 0.0f;   // the lane's pending splat: its centre and slot
+  uint32_t fslot = 0, pend = 0;
   auto flush = [&]() {
     wave_lds_order();
-    if (lane < 9 * (int)pend) {
-      const float4* q = reinterpret_cast<const float4*>(wred + 16 * lane);
-      const float4 a0 = q[0], a1 = q[1], a2 = q[2], a3 = q[3];
-      const float sum = ((a0.x + a0.y) + (a0.z + a0.w)) + ((a1.x + a1.y) + (a1.z + a1.w)) +
-                        (((a2.x + a2.y) + (a2.z + a2.w)) + ((a3.x + a3.y) + (a3.z + a3.w)));
-      const int j = (lane * 57) >> 9;   // lane / 9 for lane < 64
-      atomicAdd(gslot + 9 * (size_t)wslot[j] + (lane - 9 * j), sum);
-    }
+    const float4 d = reinterpret_cast<const float4*>(wred)[lane];
+    const float4 q = reinterpret_cast<const float4*>(wred)[64 + lane];
+    const float x0 = fcx - fu, x1 = fcx + 1.0f - fu, x2 = fcx + 2.0f - fu,
+                x3 = fcx + 3.0f - fu, y = fcy - fv;
+    const float d0 = d.x * x0, d1 = d.y * x1, d2 = d.z * x2, d3 = d.w * x3;
+    const float m0 = (d.x + d.y) + (d.z + d.w);
+    const float mx = (d0 + d1) + (d2 + d3);
+    const float mxx = fmaf(d3, x3, fmaf(d2, x2, fmaf(d1, x1, d0 * x0)));
+    const float my = m0 * y, mxy = mx * y, myy = my * y;
+    const float c0 = fmaf(q.w, h0.w, fmaf(q.z, h0.z, fmaf(q.y, h0.y, q.x * h0.x)));
+    const float c1 = fmaf(q.w, h1.w, fmaf(q.z, h1.z, fmaf(q.y, h1.y, q.x * h1.x)));
+    float c2 = fmaf(q.w, h2.w, fmaf(q.z, h2.z, fmaf(q.y, h2.y, q.x * h2.x)));
+    // fields 0..7: m0, mx, my, mxx | mxy, myy, c0, c1.  Across bit 0 a lane keeps
+    // one half of them, then one quarter across bit 1, one across bit 3
+    const float u0 = dpp_add<kXor1>(b0 ? mxy : m0, b0 ? m0 : mxy);
+    const float u1 = dpp_add<kXor1>(b0 ? myy : mx, b0 ? mx : myy);
+    const float u2 = dpp_add<kXor1>(b0 ? c0 : my, b0 ? my : c0);
+    const float u3 = dpp_add<kXor1>(b0 ? c1 : mxx, b0 ? mxx : c1);
+    const float w0 = dpp_add<kXor2>(b1 ? u2 : u0, b1 ? u0 : u2);
+    const float w1 = dpp_add<kXor2>(b1 ? u3 : u1, b1 ? u1 : u3);
+    float sum = dpp_add<kXor8>(b3 ? w1 : w0, b3 ? w0 : w1);
+    sum = dpp_add<kFrom4>(sum, sum);
+    c2 = dpp_add<kXor1>(c2, c2);
+    c2 = dpp_add<kXor2>(c2, c2);
+    c2 = dpp_add<kXor8>(c2, c2);
+    c2 = dpp_add<kRor4>(c2, c2);
+    if (field == 8) sum = c2;
+    if (field < 9 && fs < (int)pend) atomicAdd(gslot + 9 * (size_t)fslot + field, sum);
     wave_lds_order();
     pend = 0;
   };
   for (uint32_t base = rg.x; base < rg.y && act != 0; base += 64) {
     const uint32_t n = stage_batch(fetched, stage_shrink(sb, act), wlds);
-    fetched = stage_records(slots, rec, prm.slot_mask, wid);                              // batch base + 64
+    fetched = stage_records(slots, rec, prm.slot_mask, wid);          // batch base + 64
     slots = stage_slot(inst_val, (uint64_t)base + 128, rg.y, lane);   // batch base + 128
     for (uint32_t k = 0; k < n && act != 0; ++k) {
       const float4 q0 = wlds[3 * k + 0], q1 = wlds[3 * k + 1], q2 = wlds[3 * k + 2];
-      const float r[10] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w, q2.x, q2.y};
+      float r[10] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w, q2.x, q2.y};
+      // (an empty statement that keeps the whole record's reads here, in flight
+      // together, instead of half of them after the branch below)
+      __asm__ volatile("" : "+v"(r[6]), "+v"(r[7]), "+v"(r[8]), "+v"(r[9]));
+      const float dx = fx - r[0], dy = fy - r[1];
+      const float e = fmaf(dx, fmaf(r[2], dx, r[3] * dy), fmaf(r[4] * dy, dy, r[5]));
+      // The lanes that composite this splat, and those still running, are kept
+      // as scalar masks: no lane instructions for them, and a splat that no lane
+      // takes ends here (780 -> 728 us, 112 -> 103 us, in the cases above)
+      const uint64_t hit = __builtin_amdgcn_ballot_w64(e >= amin) & act;
+      if (hit == 0) continue;
       // Every lane runs the same arithmetic: a lane that has stopped, or
       // whose alpha is below alpha_min, takes a = 0 and dL/dalpha = 0, which
       // leaves its state unchanged and makes each of its terms an exact zero.
-      const float dx = fx - r[0], dy = fy - r[1];
-      const float e = fmaf(dx, fmaf(r[2], dx, r[3] * dy), fmaf(r[4] * dy, dy, r[5]));
-      const bool contrib = !done && e >= amin;
+      const bool contrib = __builtin_amdgcn_inverse_ballot_w64(hit);
       const float a = contrib ? __builtin_amdgcn_exp2f(e) : 0.0f;
       const float T_before = op.T, tau_before = op.tau;
       bool stops;
       const float p = op.step(a, param, t_eps, stops);
+      const uint64_t ends = __builtin_amdgcn_ballot_w64(stops);
       float dalpha;
       bool adds = contrib;
       if (MODEL == 0) {
@@ -190,33 +239,20 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
         dalpha = fmaf(G, fmaf(c, tau_before, 1.0f), c * thg);
         adds = contrib && !stops;   // the saturating splat takes the remainder: 0
       }
-      done = done || stops;
       // alpha = aleph exp(-q/2), q = A dx^2 + 2 B dx dy + C dy^2: with
       // da = alpha dL/dalpha a pixel adds dL/daleph = da / aleph,
       // dL/du = da (A dx + B dy), dL/dv = da (B dx + C dy) and
       // dL/d(A, B, C) = -da (dx^2 / 2, dx dy, dy^2 / 2), all linear in the
       // moments da (1, dx, dy, dx^2, dx dy, dy^2): the wave sums those, and
       // project_bwd applies the slot's aleph and conic once per slot
-      const float da = adds ? dalpha * a : 0.0f;
-      const float dax = da * dx, day = da * dy;
-      if (__builtin_amdgcn_ballot_w64(contrib) != 0) {
-        float t[9] = {quad_total(da),       quad_total(dax),      quad_total(day),
-                      quad_total(dax * dx), quad_total(dax * dy), quad_total(day * dy),
-                      quad_total(p * g0),   quad_total(p * g1),   quad_total(p * g2)};
-        // (an empty statement that keeps each sum's last add here, with every
-        // lane active, where it folds into one DPP add, instead of letting it
-        // sink into the quad leaders' store below)
-#pragma unroll
-        for (int f = 0; f < 9; ++f) __asm__ volatile("" : "+v"(t[f]));
-        if ((lane & 3) == 0) {
-          float* row = wred + 9 * 16 * pend + (lane >> 2);
-#pragma unroll
-          for (int f = 0; f < 9; ++f) row[16 * f] = t[f];
-        }
-        if (lane == 0) wslot[pend] = __float_as_uint(r[9]);
-        if (++pend == kRedSplats) flush();
-      }
-      act = __builtin_amdgcn_ballot_w64(!done);
+      wred[64 * pend + lane] = adds ? dalpha * a : 0.0f;
+      wred[64 * (kRedSplats + pend) + lane] = p;
+      const bool mine = fs == (int)pend;
+      fu = mine ? r[0] : fu;
+      fv = mine ? r[1] : fv;
+      fslot = mine ? __float_as_uint(r[9]) : fslot;
+      if (++pend == kRedSplats) flush();
+      act &= ~ends;
     }
   }
   if (pend) flush();
