@@ -120,6 +120,7 @@ struct nxs_context {
   // the tile lists lie cell by cell (two-level binning; no tile keys are kept)
   bool last_by_cell = false;
   int last_ax = 0, last_ay = 0;      // its rectangles: tiles of 2^ax x 2^ay units
+  bool last_small = false;         // its rectangles are small_rect() words
   uint32_t last_slot_mask = ~0u;     // the bits of its list entries that are the slot
   const nxs_fwd_state* last_state = nullptr;   // holds last_inst_val, if any
   // instances of the context's last known render: a deferred render's tile
@@ -525,8 +526,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   if ((st = ensure(ctx, ctx->depth_key, 4 * S, s)) || (st = ensure(ctx, ctx->dsort_a, 4 * S, s)) ||
       (st = ensure(ctx, ctx->dsort_b, 4 * S, s)) ||
       (st = ensure(ctx, ctx->slot_a, 4 * S, s)) || (st = ensure(ctx, ctx->slot_b, 4 * S, s)) ||
-      (st = ensure(ctx, ctx->trect, 8 * S, s)) ||
-      (st = ensure(ctx, ctx->rect_sorted, 8 * S, s)) ||
+      (st = ensure(ctx, ctx->trect, (bins.small ? 4 : 8) * S, s)) ||
+      (st = ensure(ctx, ctx->rect_sorted, (bins.small ? 4 : 8) * S, s)) ||
       (st = ensure(ctx, ctx->prec, 48 * S, s)) ||
       (st = ensure(ctx, ctx->counts,
                    4 * std::max(radix_counts_words(S / sort_parts, sort_parts), bin_counts_words(bins)), s)) ||
@@ -553,7 +554,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
         (st = ensure(ctx, ctx->counts, 4 * radix_counts_words(std::max<int64_t>(S, icap)), s)))
       return st;
   }
-  ProjDev proj{P<uint32_t>(ctx->depth_key), P<uint2>(ctx->trect), P<float4>(ctx->prec)};
+  ProjDev proj{P<uint32_t>(ctx->depth_key), P<uint2>(ctx->trect), bins.small,
+               P<float4>(ctx->prec)};
   GaussDev gd{g->means, g->scales, g->quats, g->opacities, g->sh, g->n, g->sh_degree};
   Counters* dcount = P<Counters>(ctx->counters);
   const float kappa2 = (float)(2.0 * std::log(1.0 / (double)c.alpha_min));
@@ -620,7 +622,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
       launch_depth_local(proj.depth_key, proj.trect, g->n, n_views, P<uint32_t>(ctx->dsort_a),
                          P<uint32_t>(ctx->slot_a), P<uint32_t>(ctx->dsort_b),
                          P<uint32_t>(ctx->slot_b), vis, P<uint32_t>(ctx->slot_b),
-                         P<uint2>(ctx->rect_sorted), s);
+                         P<uint2>(ctx->rect_sorted), bins.small, s);
       return 1;
     }
     return radix_sort_planned(P<uint32_t>(ctx->depth_key), nullptr, P<uint32_t>(ctx->dsort_a),
@@ -629,7 +631,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
                               dcount->plan, first,
                               P<uint32_t>(ctx->counts), proj.trect,
                               by_cell ? nullptr : P<uint32_t>(ctx->nt_sorted),
-                              P<uint2>(ctx->rect_sorted), s);
+                              P<uint2>(ctx->rect_sorted), bins.small, s);
   };
   // (tile first: no depth sort; the slots are binned in their own order)
   uint32_t* sorted_slots = nullptr;
@@ -794,6 +796,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   ctx->last_ax = ax;
   ctx->last_ay = ay;
   ctx->last_slot_mask = slot_mask;
+  ctx->last_small = bins.small;
 
   if (state_out) {
     // hand the buffers the backward re-reads to a new state; the context
@@ -1448,8 +1451,15 @@ nxs_status nxs_inspect_projection(nxs_context* ctx, int32_t view, uint32_t* dept
   std::vector<uint2> rect(n);
   HIP_TRY(hipMemcpy(depth_bits_host, (uint32_t*)ctx->depth_key.p + view * n, 4 * n,
                     hipMemcpyDeviceToHost));
-  HIP_TRY(hipMemcpy(rect.data(), (uint2*)ctx->trect.p + view * n, 8 * n,
-                    hipMemcpyDeviceToHost));
+  if (ctx->last_small) {
+    std::vector<uint32_t> words(n);
+    HIP_TRY(hipMemcpy(words.data(), (uint32_t*)ctx->trect.p + view * n, 4 * n,
+                      hipMemcpyDeviceToHost));
+    for (int64_t i = 0; i < n; ++i) rect[i] = wide_rect(words[i]);
+  } else {
+    HIP_TRY(hipMemcpy(rect.data(), (uint2*)ctx->trect.p + view * n, 8 * n,
+                      hipMemcpyDeviceToHost));
+  }
   for (int64_t i = 0; i < n; ++i) {
     if (rect[i].x == 0xFFFFFFFFu) {
       depth_bits_host[i] = 0;

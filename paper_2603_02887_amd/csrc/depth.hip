@@ -180,13 +180,25 @@ __device__ uint32_t sort_lds(const uint32_t* __restrict__ keys, int m, SortLds& 
   return seen;
 }
 
+// Rectangles of either kind (ProjDev): one moved, and an array's part from i on.
+__device__ __forceinline__ void copy_rect(uint2* __restrict__ to, size_t j,
+                                          const uint2* __restrict__ from, uint32_t i, bool small) {
+  if (small)
+    reinterpret_cast<uint32_t*>(to)[j] = reinterpret_cast<const uint32_t*>(from)[i];
+  else
+    to[j] = from[i];
+}
+__device__ __forceinline__ uint2* rect_at(uint2* p, size_t i, bool small) {
+  return small ? reinterpret_cast<uint2*>(reinterpret_cast<uint32_t*>(p) + i) : p + i;
+}
+
 // A bucket through memory (none of its keys culled): passes between
 // (k0, v0), where it lies, and (k1, v1), an even number of them, each counting
 // the whole bucket and then ranking and moving it kNT ITEMS keys at a time.
 template <int ITEMS>
 __device__ void sort_memory(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int m,
                             const uint2* __restrict__ trect, uint32_t* slots_out,
-                            uint2* __restrict__ rect_out, SortLds& S) {
+                            uint2* __restrict__ rect_out, bool small, SortLds& S) {
   constexpr int CAP = kNT * ITEMS, NW = kNT / 64;
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   uint32_t mn = kCulled, mx = 0u;
@@ -274,7 +286,7 @@ __device__ void sort_memory(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* 
   for (int i = t; i < m; i += kNT) {   // (back in v0)
     const uint32_t slot = v0[i];
     slots_out[i] = slot;
-    rect_out[i] = trect[slot];
+    copy_rect(rect_out, i, trect, slot, small);
   }
 }
 
@@ -303,7 +315,7 @@ __device__ uint32_t compact(const uint32_t* __restrict__ keys, uint32_t first, i
 __global__ __launch_bounds__(kNT) void depth_local_kernel(
     const uint32_t* __restrict__ depth_key, int32_t n, uint32_t* key_tmp, uint32_t* slot_tmp,
     uint32_t* key_alt, uint32_t* slot_alt, const uint2* __restrict__ trect,
-    uint32_t* __restrict__ vis, uint32_t* slots_out, uint2* __restrict__ rect_out) {
+    uint32_t* __restrict__ vis, uint32_t* slots_out, uint2* __restrict__ rect_out, bool small) {
   __shared__ SortLds S;
   const size_t base = (size_t)blockIdx.x * (uint32_t)n;
   const uint32_t* keys = depth_key + base;
@@ -313,12 +325,12 @@ __global__ __launch_bounds__(kNT) void depth_local_kernel(
     for (int i = threadIdx.x; i < (int)seen; i += kNT) {
       const uint32_t slot = (uint32_t)base + S.out[i];
       slots_out[base + i] = slot;
-      rect_out[base + i] = trect[slot];
+      copy_rect(rect_out, base + i, trect, slot, small);
     }
   } else {
     seen = compact(keys, (uint32_t)base, n, key_tmp + base, slot_tmp + base, S.a);
     sort_memory<4>(key_tmp + base, slot_tmp + base, key_alt + base, slot_alt + base, (int)seen,
-                   trect, slots_out + base, rect_out + base, S);
+                   trect, slots_out + base, rect_at(rect_out, base, small), small, S);
   }
   if (threadIdx.x == 0) vis[blockIdx.x] = seen;
 }
@@ -328,10 +340,10 @@ __global__ __launch_bounds__(kNT) void depth_local_kernel(
 void launch_depth_local(const uint32_t* depth_key, const uint2* trect, int32_t n, int n_views,
                         uint32_t* key_tmp, uint32_t* slot_tmp, uint32_t* key_alt,
                         uint32_t* slot_alt, uint32_t* vis, uint32_t* slots_out, uint2* rect_out,
-                        hipStream_t s) {
+                        bool small, hipStream_t s) {
   if (n <= 0) return;
   hipLaunchKernelGGL(depth_local_kernel, dim3(n_views), dim3(kNT), 0, s, depth_key, n, key_tmp,
-                     slot_tmp, key_alt, slot_alt, trect, vis, slots_out, rect_out);
+                     slot_tmp, key_alt, slot_alt, trect, vis, slots_out, rect_out, small);
 }
 
 }  // namespace nxs

@@ -43,8 +43,9 @@ struct ProjDev {
   uint32_t* depth_key;      // float32 depth bits; 0xFFFFFFFF when culled
   // rectangle (x0 | x1 << 16, y0 | y1 << 16), all ones when culled: in blocks
   // of 8x8 pixels for the two-level binning (the tiles it covers are
-  // tile_rect() of it), else in tiles
+  // tile_rect() of it), else in tiles; `small`: as small_rect() words
   uint2* trect;
+  bool small;
   // 3 float4 per slot:
   //   (u_hi, u_lo, v_hi, v_lo)  image-plane centre as float hi + lo parts
   //   (A', B', C', log2 aleph)  log2(alpha) = log2 aleph + A' dx^2 + B' dx dy + C' dy^2
@@ -169,6 +170,26 @@ __host__ __device__ __forceinline__ uint2 tile_rect(uint2 r, int ax, int ay) {
   return r;
 }
 
+// A rectangle in one word (x0 | y0 << 8 | x1 << 16 | y1 << 24), where no
+// coordinate exceeds 254; all ones when culled.
+constexpr int kSmallRectBlocks = 255;
+__host__ __device__ __forceinline__ uint32_t small_rect(uint2 r) {
+  return r.x == 0xFFFFFFFFu ? 0xFFFFFFFFu : (r.x | (r.y << 8));
+}
+__host__ __device__ __forceinline__ uint2 wide_rect(uint32_t w) {
+  const bool culled = w == 0xFFFFFFFFu;
+  uint2 r;
+  r.x = culled ? w : w & 0x00FF00FFu;
+  r.y = culled ? w : (w >> 8) & 0x00FF00FFu;
+  return r;
+}
+// rectangle i of an array of either kind
+template <bool SMALL>
+__device__ __forceinline__ uint2 load_rect(const uint2* rects, int64_t i) {
+  if (SMALL) return wide_rect(reinterpret_cast<const uint32_t*>(rects)[i]);
+  return rects[i];
+}
+
 // The tiles a slot's rectangle covers (0 for a culled slot).
 __device__ __forceinline__ uint32_t rect_tile_count(uint2 r) {
   if (r.x == 0xFFFFFFFFu) return 0u;
@@ -233,12 +254,13 @@ int radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
 // (the caller checks plan[0] once it has read the counters, and sorts again
 // with first_pass = 0 otherwise).  The result is in (k1, v1); returns 1.
 // The last pass also writes, in sorted order, each value's tile rectangle
-// from `trect` (indexed by value) into rect_out, and its tile count into
-// nt_out unless that is null.
+// from `trect` (indexed by value; both arrays of small_rect() words if `small`)
+// into rect_out, and its tile count into nt_out unless that is null.
 int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0,
                        uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int parts,
                        const uint32_t* plan, int first_pass, uint32_t* counts,
-                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, hipStream_t s);
+                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small,
+                       hipStream_t s);
 
 // Depth sort of views of n <= kLocalMax slots each, one work-group per view
 // (depth.hip), stable: the slots of view v's visible Gaussians and their tile
@@ -248,7 +270,7 @@ constexpr int kLocalMax = 8192;
 void launch_depth_local(const uint32_t* depth_key, const uint2* trect, int32_t n, int n_views,
                         uint32_t* key_tmp, uint32_t* slot_tmp, uint32_t* key_alt,
                         uint32_t* slot_alt, uint32_t* vis, uint32_t* slots_out, uint2* rect_out,
-                        hipStream_t s);
+                        bool small, hipStream_t s);
 
 // Binning in two levels (bin.hip): each view's slots, in depth order or in slot
 // order (sorted_slots null), are dealt to cells of 2^sx x 2^sy tiles, and each
@@ -271,6 +293,7 @@ struct BinPlan {
   int sx, sy;         // log2 of a cell's tiles per row and column
   int ax, ay;         // log2 of a tile's 8x8 blocks per row and column
   bool pack;
+  bool small;         // the rectangles are small_rect() words
   uint32_t n_cells;   // 0: the two-level binning does not apply
   int32_t n;          // slots per view
   int n_views;

@@ -447,7 +447,10 @@ __global__ __launch_bounds__(kBlock) void project_kernel(
       rec[2] = make_float4(rgb[0], rgb[1], rgb[2], __uint_as_float(hx | (hy << 16)));
     }
     out.depth_key[slot] = kg.depth_bits;
-    out.trect[slot] = rect;
+    if (out.small)
+      reinterpret_cast<uint32_t*>(out.trect)[slot] = small_rect(rect);
+    else
+      out.trect[slot] = rect;
     nt_sum += nt;
   }
   // block reductions: instance total and visible depth-bit range

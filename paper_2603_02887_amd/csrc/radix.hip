@@ -234,8 +234,8 @@ __global__ __launch_bounds__(kRThreads) void rx_scan(uint32_t* __restrict__ coun
 
 // vals_in == nullptr: the values are the input positions.  The last pass
 // also writes each value's tile rectangle (from `trect`) when trect is given,
-// and its tile count when nt_out is.
-template <int ITEMS>
+// and its tile count when nt_out is (SMALL: as words, without the counts).
+template <int ITEMS, bool SMALL>
 __global__ __launch_bounds__(kRThreads) void rx_scatter(
     const uint32_t* keys_in, const uint32_t* vals_in, const uint32_t* keys_first,
     const uint32_t* vals_first, uint32_t* __restrict__ keys_out,
@@ -374,9 +374,14 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
         keys_out[g] = k;
         vals_out[g] = v;
         if (trect) {   // the slot's tile rectangle, now in sorted order
-          const uint2 rc = trect[v];
-          if (nt_out) nt_out[g] = rect_tile_count(rc);
-          rect_out[g] = rc;
+          if (SMALL) {
+            reinterpret_cast<uint32_t*>(rect_out)[g] =
+                reinterpret_cast<const uint32_t*>(trect)[v];
+          } else {
+            const uint2 rc = trect[v];
+            if (nt_out) nt_out[g] = rect_tile_count(rc);
+            rect_out[g] = rc;
+          }
         }
       }
     }
@@ -752,7 +757,7 @@ namespace {
 int run_passes(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, uint32_t* v0,
                uint32_t* k1, uint32_t* v1, int64_t n, int first, int passes,
                const int* shifts, const int* widths, const uint32_t* plan, uint32_t* counts,
-               const uint2* trect, uint32_t* nt_out, uint2* rect_out, hipStream_t s,
+               const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small, hipStream_t s,
                const Counters* dn, int64_t n_plan, int parts = 1) {
   // n (per part) bounds the keys (the counts layout); the grid is planned for n_plan
   // keys (with dn, the count expected on the device) and loops beyond it
@@ -772,23 +777,21 @@ int run_passes(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
     uint32_t* vout = (p & 1) ? v1 : v0;
     const dim3 scan_grid(plan ? kRBins : (1u << width), parts);
     const bool last = p == passes - 1;
-    if (large) {
-      hipLaunchKernelGGL(rx_count<kRItemsLarge>, dim3(grid), dim3(kRThreads), 0, s, kin,
-                         keys_in, n, shift, width, plan, p, (uint32_t)parts, nchunks, per, counts, dn);
-      hipLaunchKernelGGL(rx_scan<kRItemsLarge>, scan_grid, dim3(kRThreads), 0, s, counts,
-                         nchunks, totals, width, plan, p, n, dn);
-      hipLaunchKernelGGL(rx_scatter<kRItemsLarge>, dim3(grid), dim3(kRThreads), 0, s, kin, vin,
-                         keys_in, vals_in, kout, vout, n, shift, width, plan, p,
-                         (uint32_t)parts, nchunks, per, counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
-    } else {
-      hipLaunchKernelGGL(rx_count<kRItemsSmall>, dim3(grid), dim3(kRThreads), 0, s, kin,
-                         keys_in, n, shift, width, plan, p, (uint32_t)parts, nchunks, per, counts, dn);
-      hipLaunchKernelGGL(rx_scan<kRItemsSmall>, scan_grid, dim3(kRThreads), 0, s, counts,
-                         nchunks, totals, width, plan, p, n, dn);
-      hipLaunchKernelGGL(rx_scatter<kRItemsSmall>, dim3(grid), dim3(kRThreads), 0, s, kin, vin,
-                         keys_in, vals_in, kout, vout, n, shift, width, plan, p,
-                         (uint32_t)parts, nchunks, per, counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
-    }
+    auto pass = [&](auto count, auto scan, auto scatter) {
+      hipLaunchKernelGGL(count, dim3(grid), dim3(kRThreads), 0, s, kin, keys_in, n, shift, width,
+                         plan, p, (uint32_t)parts, nchunks, per, counts, dn);
+      hipLaunchKernelGGL(scan, scan_grid, dim3(kRThreads), 0, s, counts, nchunks, totals, width,
+                         plan, p, n, dn);
+      hipLaunchKernelGGL(scatter, dim3(grid), dim3(kRThreads), 0, s, kin, vin, keys_in, vals_in,
+                         kout, vout, n, shift, width, plan, p, (uint32_t)parts, nchunks, per,
+                         counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
+    };
+    if (large)
+      pass(rx_count<kRItemsLarge>, rx_scan<kRItemsLarge>,
+           last && small ? rx_scatter<kRItemsLarge, true> : rx_scatter<kRItemsLarge, false>);
+    else
+      pass(rx_count<kRItemsSmall>, rx_scan<kRItemsSmall>,
+           last && small ? rx_scatter<kRItemsSmall, true> : rx_scatter<kRItemsSmall, false>);
     kin = kout;
     vin = vout;
   }
@@ -810,17 +813,18 @@ int radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
     shift += widths[p];
   }
   return run_passes(keys_in, vals_in, k0, v0, k1, v1, n, 0, passes, shifts, widths, nullptr,
-                    counts, nullptr, nullptr, nullptr, s, dn,
+                    counts, nullptr, nullptr, nullptr, false, s, dn,
                     dn && n_plan > 0 ? std::min(n_plan, n) : n);
 }
 
 int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0,
                        uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int parts,
                        const uint32_t* plan, int first_pass, uint32_t* counts,
-                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, hipStream_t s) {
+                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small,
+                       hipStream_t s) {
   if (n <= 0) return 1;
   return run_passes(keys_in, vals_in, k0, v0, k1, v1, n, first_pass, kPlanPasses, nullptr,
-                    nullptr, plan, counts, trect, nt_out, rect_out, s, nullptr, n, parts);
+                    nullptr, plan, counts, trect, nt_out, rect_out, small, s, nullptr, n, parts);
 }
 
 void launch_tile_depth_sort(const uint2* ranges, int64_t n_tiles, const uint32_t* depth_key,
