@@ -70,11 +70,11 @@ HBM_PEAK_GBS = 8000.0
 # size (profiles/forward_hbm_traffic_scene1m_1080p.md).  They describe the
 # kernel sources with this digest and are reported as null once those change.
 TRAFFIC_SOURCES = ("composite.hip", "nxs_ops.h", "nxs_stage.h", "nxs_internal.h")
-TRAFFIC = {"digest": "4dbd297174eaaed7865081fbd6d73b76f50b9775b3666197a56c27f04d2d49aa",
+TRAFFIC = {"digest": "c20a0206352d4c4321e69bec35929240f80d2fdcfc2f1abbf861f0214ba677ec",
            "tile": "16x16",
            "bytes": {
-               "queue": {0: 485824065, 1: 253662114, 2: 287820851, 3: 240616214},
-               "tiles": {0: 225022077, 1: 131614891, 2: 145831234, 3: 127215006}}}
+               "queue": {0: 295754059, 1: 165880810, 2: 184941911, 3: 160143950},
+               "tiles": {0: 215889894, 1: 123659493, 2: 136976199, 3: 119775502}}}
 
 
 def measured_traffic(model, tile, schedule):

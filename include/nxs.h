@@ -7,9 +7,9 @@
  * formation of Sec. 4 of "Generalized non-exponential Gaussian splatting"
  * (eq. generalized_gaussian with the discrete extinction of eq. nexp_p and
  * the operators of Table 1).  Each call runs, on the caller's HIP stream:
- * EWA projection, depth sort, tile binning, a stable tile sort, tile ranges,
- * and a per-tile composite that gathers each tile's splats in sorted order
- * batch by batch into on-chip memory.
+ * EWA projection, depth sort, a stable binning by tile, and a per-tile
+ * composite that gathers each tile's splats in sorted order batch by batch
+ * into on-chip memory.
  *
  * Conventions common to every entry point
  *   - Array pointers are DEVICE pointers of the context's device, unless the
@@ -142,17 +142,17 @@ typedef struct {
   int32_t schedule;       /* nxs_schedule of the composite; 0 -> NXS_SCHED_QUEUE */
   float instance_hint;    /* deferred renders: the tile instances the caller
                              expects (0 -> the context's last count); sizes the
-                             tile sort's launches, never the result */
+                             binning's launches, never the result */
   int32_t sort_order;     /* nxs_sort_order; 0 -> NXS_SORT_AUTO */
 } nxs_render_opts;
 
 /* How the per-tile front-to-back lists are built (bitwise the same lists,
  * ordered by tile, float32 depth bits, Gaussian index):
- *   DEPTH_FIRST  sort all projected Gaussians by depth, emit their tile
- *                instances in that order, sort the instances stably by tile
- *   TILE_FIRST   emit instances in Gaussian order, sort them stably by tile,
- *                then sort each tile's list by depth in on-chip memory (a list
- *                longer than 4,096 entries is sorted through device memory)
+ *   DEPTH_FIRST  sort all projected Gaussians by depth, bin them stably by
+ *                tile in that order
+ *   TILE_FIRST   bin the Gaussians stably by tile in their own order, then sort
+ *                each tile's list by depth in on-chip memory (a list longer
+ *                than 4,096 entries is sorted through device memory)
  *   AUTO         TILE_FIRST when the expected instances per tile (the
  *                caller's instance_hint, else the context's last count) are
  *                at most 1,024 on average, else DEPTH_FIRST */
@@ -164,11 +164,11 @@ typedef enum {
 
 /* opts.flags
  *   NXS_FLAG_DEFERRED  the forward does not wait on the host for the
- *       instance count: the instance buffers and the grids of the tile sort
+ *       instance count: the instance buffers and the grids of the binning
  *       are sized from the context's current capacity (what earlier renders
  *       needed, with headroom).  A render that needs more instances than that
  *       (or a depth sort of more passes than the context planned) is detected
- *       on the device, does no work after the emission (its outputs are the
+ *       on the device, does no work after the binning (its outputs are the
  *       background) and is reported by the next nxs_forward_status, which
  *       also grows the capacity so that repeating the render succeeds.
  *       Results are bitwise those of a render that waits. */
@@ -481,8 +481,9 @@ nxs_status nxs_measure_peaks(nxs_context* ctx, double* fp32_fma_tflops, double* 
 /* Per-stage GPU timing.  With timing enabled, each render records hipEvents
  * on its stream between its stages; nxs_inspect_stage_times then returns the
  * milliseconds of the last render's stages, in this order:
- *   0 projection, 1 depth sort, 2 instance emission, 3 tile sort,
- *   4 tile ranges (and the tile order of the queue schedules), 5 composite
+ *   0 projection, 1 depth sort, 2 binning into cells of tiles (or instance
+ *   emission), 3 the cells' lists into the tiles' with their ranges (or the tile
+ *   sort), 4 the tile order of the queue schedules (or tile ranges too), 5 composite
  *   (with the gather of the splats it reaches).
  * ms_host has n >= NXS_N_STAGES entries.  Waits for the last render. */
 #define NXS_N_STAGES 6

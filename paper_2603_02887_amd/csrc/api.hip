@@ -530,7 +530,9 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
       (st = ensure(ctx, ctx->rect_sorted, (bins.small ? 4 : 8) * S, s)) ||
       (st = ensure(ctx, ctx->prec, 48 * S, s)) ||
       (st = ensure(ctx, ctx->counts,
-                   4 * std::max(radix_counts_words(S / sort_parts, sort_parts), bin_counts_words(bins)), s)) ||
+                   4 * std::max(radix_counts_words(S / sort_parts, sort_parts),
+                                bin_counts_words(bins)),
+                   s)) ||
       (st = ensure(ctx, ctx->ranges, 8 * total_tiles + 4 * kSchedCounters, s)))
     return st;
   if (by_cell) {
@@ -592,7 +594,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   // counters)
   if (!launch_project(gd, P<ViewDev>(ctx->views), by_arg ? host_views : nullptr, n_views,
                       kappa2, c.alpha_min, bit_length((uint64_t)tw) - 1 - ax,
-                      bit_length((uint64_t)th) - 1 - ay, ax, ay, proj, P<uint4>(ctx->partials), dcount, chk,
+                      bit_length((uint64_t)th) - 1 - ay, ax, ay, proj,
+                      P<uint4>(ctx->partials), dcount, chk,
                       P<uint32_t>(ctx->ranges), 2 * total_tiles + kSchedCounters, s))
     return fail(ctx, NXS_EHIP, "the view table could not be passed to the projection");
   HIP_TRY(hipGetLastError());

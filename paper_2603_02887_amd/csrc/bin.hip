@@ -156,8 +156,9 @@ __device__ __forceinline__ ChunkOf chunk_of(uint32_t c, uint32_t cpv, uint32_t c
 template <bool SMALL>
 __global__ __launch_bounds__(kBThreads) void cell_count_kernel(
     const uint2* __restrict__ rects, int32_t n, const uint32_t* __restrict__ vis,
-    uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per, const ViewDev* __restrict__ views, CellShape shape,
-    uint32_t* __restrict__ counts, const Counters* __restrict__ cnt) {
+    uint32_t nchunks, uint32_t cpv, uint32_t chunk, uint32_t per,
+    const ViewDev* __restrict__ views, CellShape shape, uint32_t* __restrict__ counts,
+    const Counters* __restrict__ cnt) {
   __shared__ uint32_t h[kViewCells];
   if (cnt->fail) return;
   const uint32_t c = banded_chunk(blockIdx.x, per);
@@ -738,12 +739,12 @@ void fine_t(const BinPlan& p, const BinBuffers& b, uint64_t m_plan, const ViewDe
   // a wave per segment, looping beyond the grid
   const uint64_t segs = (m_plan >> p.seg_shift) + p.n_cells;
   const unsigned grid = (unsigned)std::min<uint64_t>((segs + kBWaves - 1) / kBWaves, kMaxFineGrid);
-  hipLaunchKernelGGL((seg_count_kernel<SX, SY, AX, AY>), dim3(grid), dim3(kBThreads), 0, s, b.pair_rect,
-                     a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs, counters);
+  hipLaunchKernelGGL((seg_count_kernel<SX, SY, AX, AY>), dim3(grid), dim3(kBThreads), 0, s,
+                     b.pair_rect, a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs, counters);
   hipLaunchKernelGGL((cell_tiles_kernel<SX, SY>), dim3(p.n_cells), dim3(kBThreads), 0, s, views,
                      p.n_views, a.seg0, a.inst0, b.segs, b.ranges, counters);
-  hipLaunchKernelGGL((seg_emit_kernel<SX, SY, AX, AY>), dim3(grid), dim3(kBThreads), 0, s, b.pair_slot,
-                     b.pair_rect, a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs,
+  hipLaunchKernelGGL((seg_emit_kernel<SX, SY, AX, AY>), dim3(grid), dim3(kBThreads), 0, s,
+                     b.pair_slot, b.pair_rect, a.pair0, a.seg0, p.n_cells, p.seg_shift, b.segs,
                      p.pack ? ~kPackMask : 0u, b.list, counters);
 }
 
@@ -767,8 +768,8 @@ void launch_bin_count(const BinPlan& p, const BinBuffers& b, const uint2* rects,
   const CellArrays a = cell_arrays(p, b);
   const uint32_t nchunks = p.cpv * p.n_views, per = (nchunks + kXcds - 1) / kXcds;
   hipLaunchKernelGGL(p.small ? cell_count_kernel<true> : cell_count_kernel<false>,
-                     dim3(per * kXcds), dim3(kBThreads), 0, s, rects, p.n, vis, nchunks, p.cpv, (uint32_t)p.chunk, per, views, shape_of(p), b.counts,
-                     counters);
+                     dim3(per * kXcds), dim3(kBThreads), 0, s, rects, p.n, vis, nchunks,
+                     p.cpv, (uint32_t)p.chunk, per, views, shape_of(p), b.counts, counters);
   hipLaunchKernelGGL(cell_scan_kernel, dim3(p.n_cells), dim3(kBThreads), 0, s, b.counts, p.cpv,
                      a.totals, a.weights, counters);
   hipLaunchKernelGGL(cell_starts_kernel, dim3(1), dim3(kStartThreads), 0, s, a.totals, a.weights,
@@ -782,8 +783,8 @@ void launch_bin_scatter(const BinPlan& p, const BinBuffers& b, const uint32_t* s
   const CellArrays a = cell_arrays(p, b);
   const uint32_t nchunks = p.cpv * p.n_views, per = (nchunks + kXcds - 1) / kXcds;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, sorted_slots, rects, p.n, vis,
-                       nchunks, p.cpv, (uint32_t)p.chunk, per, views, shape_of(p), b.counts,
+    hipLaunchKernelGGL(kernel, dim3(per * kXcds), dim3(kBThreads), 0, s, sorted_slots, rects,
+                       p.n, vis, nchunks, p.cpv, (uint32_t)p.chunk, per, views, shape_of(p), b.counts,
                        a.pair0, capacity, b.pair_slot, b.pair_rect, counters);
   };
   if (p.chunk >= 512)

@@ -151,7 +151,7 @@ __device__ __forceinline__ void composite_block(
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       n += stage_batch(fetched[k], sbr, wlds + 3 * n);
-      fetched[k] = stage_records(slots[k], rec, prm.slot_mask, wid);                                 // next round
+      fetched[k] = stage_records(slots[k], rec, prm.slot_mask, wid);   // next round
       slots[k] = stage_slot(inst_val, (uint64_t)base + 2 * kRound + 64u * k, rg.y, lane);
     }
     // two staged splats per trip: an odd count (below 64 NB, so the stage has

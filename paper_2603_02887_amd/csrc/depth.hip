@@ -77,7 +77,8 @@ __device__ __forceinline__ void block_range(uint32_t& mn, uint32_t& mx, uint32_t
 // items li >= m take part as nothing.
 template <int ITEMS>
 __device__ __forceinline__ void wave_ranks(const uint32_t (&k)[ITEMS], int m, int shift, int width,
-                                           SortLds& S, uint32_t (&dig)[ITEMS], uint32_t (&rank)[ITEMS]) {
+                                           SortLds& S, uint32_t (&dig)[ITEMS],
+                                           uint32_t (&rank)[ITEMS]) {
   constexpr int G = ITEMS < 4 ? ITEMS : 4;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t mask = (1u << width) - 1u;

@@ -318,7 +318,8 @@ size_t bin_seg_words(const BinPlan& p, uint64_t max_pairs);
 // Pairs per chunk and cell, and their first positions.
 // (vis: the slots of each view to take, the first of its part; null: all)
 void launch_bin_count(const BinPlan& p, const BinBuffers& b, const uint2* rects,
-                      const uint32_t* vis, const ViewDev* views, const Counters* counters, hipStream_t s);
+                      const uint32_t* vis, const ViewDev* views, const Counters* counters,
+                      hipStream_t s);
 // The pairs into their cells' lists; nothing if the render has more than
 // `capacity` instances.
 void launch_bin_scatter(const BinPlan& p, const BinBuffers& b, const uint32_t* sorted_slots,

@@ -267,8 +267,8 @@ __device__ void fold_partials(const uint4* partials, int nblocks, Counters* c,
 template <int DEG, bool ARGS>
 __global__ __launch_bounds__(kBlock) void project_kernel(
     GaussDev g, ViewDev* __restrict__ views, ViewArgs va, int n_views, float kappa2,
-    float alpha_min, int unit_x, int unit_y, int ax, int ay, ProjDev out, uint4* __restrict__ partials,
-    uint32_t* __restrict__ clear, int64_t n_clear) {
+    float alpha_min, int unit_x, int unit_y, int ax, int ay, ProjDev out,
+    uint4* __restrict__ partials, uint32_t* __restrict__ clear, int64_t n_clear) {
   constexpr int K = (DEG + 1) * (DEG + 1);
   if (ARGS && blockIdx.x == 0) {
     constexpr int kWords = (int)(sizeof(ViewDev) / 4);
