@@ -135,7 +135,8 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
   Op<MODEL> op;
   // running lanes; each batch is staged against the rows and columns that
   // still hold one
-  uint64_t act = __builtin_amdgcn_ballot_w64(inside);
+  // (none where t_eps > 1, as in the forward)
+  uint64_t act = __builtin_amdgcn_ballot_w64(inside && !op.stopped(t_eps));
   // (an empty tile fetches nothing: its range is [0, 0) or [x, x))
   StageSlot slots{0u, false};
   StageFetch fetched{};

@@ -38,3 +38,14 @@ def test_sums_of_few_splats(R, n, model, op):  # noqa: F811
             got = float(np.sum(G[field] * d))
             tol = 2e-3 * float(np.sum(np.abs(G[field] * d))) + 1e-7
             assert abs(got - want) <= tol, (field, got, want)
+
+
+@pytest.mark.parametrize("n", [1, 6])
+def test_pixels_stopped_from_the_start(R, n):  # noqa: F811
+    """t_eps > 1: the forward composites nothing, so every gradient is zero."""
+    sc = synth.random_scene(5, n, mean_lo=-0.4, mean_hi=0.4, log_scale=(-1.6, 0.3))
+    cams = [synth.look_at_camera((0, 0, -3.0), width=13, height=9)]
+    F = fd.FrozenLoss(sc, cams, O.EXPONENTIAL, t_eps=0.0, seed=n)
+    G = _gpu_grads(R, sc, cams, F, 0, t_eps=1.5)
+    for k, v in G.items():
+        assert not v.any(), k
