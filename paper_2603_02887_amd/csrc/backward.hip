@@ -63,8 +63,10 @@ constexpr int kRor4 = 0x124;                               // row_ror:4
 constexpr int kRedSplats = 4;
 constexpr int kRedF4 = 2 * kRedSplats * 64 / 4;  // float4 per wave
 
+// (six waves a SIMD: left to itself the compiler takes 82 registers for the
+// quadratic operators, two more than six waves have)
 template <int MODEL, int TW, int TH>
-__global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
+__global__ __launch_bounds__(TW* TH, 6) void composite_bwd_kernel(
     const ViewDev* __restrict__ views, int n_views, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ inst_val, const float4* __restrict__ rec, CompositeParams prm,
     const float4* __restrict__ pstate, float* __restrict__ gslot, uint32_t n_tiles,
@@ -120,17 +122,20 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
     s1 = st[1];
     s2 = st[2];
   }
-  // Only the projections of the channels on the upstream gradient are needed
-  // (g . x over rgb and T, whose emission is 0 and background 1), so one
-  // number per pixel replaces four:
-  // exponential: g . the radiance not yet attributed, and g . L_b
-  float Rg = g0 * s0.x + g1 * s0.y + g2 * s0.z + gT * s0.w;
-  const float bgg = g0 * prm.bg[0] + g1 * prm.bg[1] + g2 * prm.bg[2] + gT;
-  // linear / quadratic: g . E_k and g . Theta
+  // (the fourth channel is T, whose emission is 0 and background 1)
+  // exponential: the radiance not yet attributed
+  float R0 = s0.x, R1 = s0.y, R2 = s0.z;
+  const float RT = gT * s0.w;
+  // linear / quadratic: E_k, and g . Theta.  (Emissions are subtracted channel by
+  // channel before they meet g: splats of one surface have nearly equal ones, and
+  // g . E - g . E_k would keep the rounding of two large numbers.  In float32, of
+  // emissions within 0.001 of each other, the linear operator's da is 5e-8 off
+  // this way, as with all in four channels, and 3.5e-5 off that way.)
+  const float k0 = s1.x, k1 = s1.y, k2 = s1.z;
   const float k3 = s0.w == 0.0f ? 0.0f : 1.0f;   // (saturated: 0)
-  const float kg = g0 * s1.x + g1 * s1.y + g2 * s1.z + gT * k3;
-  float thg = g0 * (s2.x - s1.x * s1.w) + g1 * (s2.y - s1.y * s1.w) +
-              g2 * (s2.z - s1.z * s1.w) - gT * (k3 * s1.w);
+  const float kT = gT * k3;
+  float thg = g0 * (s2.x - k0 * s1.w) + g1 * (s2.y - k1 * s1.w) + g2 * (s2.z - k2 * s1.w) -
+              kT * s1.w;
 
   Op<MODEL> op;
   // running lanes; each batch is staged against the rows and columns that
@@ -230,14 +235,22 @@ __global__ __launch_bounds__(TW* TH) void composite_bwd_kernel(
       bool adds = contrib;
       if (MODEL == 0) {
         const float G = fmaf(g0, r[6], fmaf(g1, r[7], g2 * r[8]));   // g . E
-        Rg = fmaf(-G, p, Rg);
+        R0 = fmaf(-r[6], p, R0);
+        R1 = fmaf(-r[7], p, R1);
+        R2 = fmaf(-r[8], p, R2);
+        const float Rg = fmaf(g0, R0, fmaf(g1, R1, fmaf(g2, R2, RT)));
         // (1 - a > 0 unless the splat stops the pixel: one with a = 1 leaves T = 0)
-        const float behind = stops ? T_before * bgg : __builtin_amdgcn_rcpf(1.0f - a) * Rg;
-        dalpha = fmaf(T_before, G, -behind);
+        dalpha = fmaf(T_before, G, -(__builtin_amdgcn_rcpf(1.0f - a) * Rg));
+        if (ends & hit) {   // (uniform; once a pixel) only the background lies behind
+          const float e0 = r[6] - prm.bg[0], e1 = r[7] - prm.bg[1], e2 = r[8] - prm.bg[2];
+          const float last = T_before * fmaf(g0, e0, fmaf(g1, e1, fmaf(g2, e2, -gT)));
+          dalpha = stops ? last : dalpha;
+        }
       } else {
-        const float G = fmaf(g0, r[6], fmaf(g1, r[7], fmaf(g2, r[8], -kg)));   // g . (E - E_k)
+        const float e0 = r[6] - k0, e1 = r[7] - k1, e2 = r[8] - k2;
+        const float G = fmaf(g0, e0, fmaf(g1, e1, fmaf(g2, e2, -kT)));   // g . (E - E_k)
         thg = fmaf(-G, a, thg);
-        dalpha = fmaf(G, fmaf(c, tau_before, 1.0f), c * thg);
+        dalpha = fmaf(c, fmaf(G, tau_before, thg), G);
         adds = contrib && !stops;   // the saturating splat takes the remainder: 0
       }
       // alpha = aleph exp(-q/2), q = A dx^2 + 2 B dx dy + C dy^2: with
