@@ -523,21 +523,21 @@ __global__ __launch_bounds__(kBThreads) void seg_count_kernel(
   const uint32_t n_seg = s_seg[n_cells];
   for (uint32_t sg = blockIdx.x * kBWaves + wid; sg < n_seg; sg += gridDim.x * kBWaves) {
     const uint32_t d = cell_of_segment(s_seg, n_cells, sg);
-    const uint32_t first = pair0[d] + ((sg - s_seg[d]) << seg_shift);
-    const uint32_t end = min(first + (1u << seg_shift), pair0[d + 1]);
+    const PairRange pr = segment_pairs(pair0[d], pair0[d + 1], sg - s_seg[d], seg_shift);
+    const uint16_t* rects = pair_rect + pr.first;
     uint32_t n[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) n[t] = 0;
-    for (uint32_t p = first; p < end; p += 256) {
+    for (uint32_t p = 0; p < pr.n; p += 256) {
       uint32_t lr[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const uint32_t i = p + 64 * q + lane;
-        lr[q] = i < end ? pair_rect[i] : 0u;
+        lr[q] = i < pr.n ? rects[i] : 0u;
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const auto m = pair_blocks<SX, SY, AX, AY>(lr[q], p + 64 * q + lane < end);
+        const auto m = pair_blocks<SX, SY, AX, AY>(lr[q], p + 64 * q + lane < pr.n);
 #pragma unroll
         for (int t = 0; t < NT; ++t) n[t] += (uint32_t)__popcll(__ballot(m.tile(t) != 0u));
       }
@@ -625,25 +625,26 @@ __global__ __launch_bounds__(kBThreads) void seg_emit_kernel(
   const uint32_t n_seg = s_seg[n_cells];
   for (uint32_t sg = blockIdx.x * kBWaves + wid; sg < n_seg; sg += gridDim.x * kBWaves) {
     const uint32_t d = cell_of_segment(s_seg, n_cells, sg);
-    const uint32_t first =
-        __builtin_amdgcn_readfirstlane(pair0[d] + ((sg - s_seg[d]) << seg_shift));
-    const uint32_t end =
-        __builtin_amdgcn_readfirstlane(min(first + (1u << seg_shift), pair0[d + 1]));
+    const PairRange pr = segment_pairs(pair0[d], pair0[d + 1], sg - s_seg[d], seg_shift);
+    const uint32_t first = __builtin_amdgcn_readfirstlane(pr.first);
+    const uint32_t n = __builtin_amdgcn_readfirstlane(pr.n);
+    const uint32_t* slots = pair_slot + first;
+    const uint16_t* rects = pair_rect + first;
     const uint32_t mine = lane < NT ? segs[(size_t)sg * NT + lane] : 0u;
     uint32_t at[NT];   // next list position of each tile (wave-uniform)
 #pragma unroll
     for (int t = 0; t < NT; ++t) at[t] = (uint32_t)__builtin_amdgcn_readlane((int)mine, t);
     uint32_t slot_n = 0, lr_n = 0;
-    if (first + lane < end) {
-      slot_n = pair_slot[first + lane];
-      lr_n = pair_rect[first + lane];
+    if ((uint32_t)lane < n) {
+      slot_n = slots[lane];
+      lr_n = rects[lane];
     }
-    for (uint32_t p = first; p < end; p += 64) {
+    for (uint32_t p = 0; p < n; p += 64) {
       const uint32_t slot = slot_n;
-      const auto m = pair_blocks<SX, SY, AX, AY>(lr_n, p + lane < end);
-      if (p + 64 + lane < end) {   // (the next 64 pairs' reads in flight meanwhile)
-        slot_n = pair_slot[p + 64 + lane];
-        lr_n = pair_rect[p + 64 + lane];
+      const auto m = pair_blocks<SX, SY, AX, AY>(lr_n, p + lane < n);
+      if (p + 64 + lane < n) {   // (the next 64 pairs' reads in flight meanwhile)
+        slot_n = slots[p + 64 + lane];
+        lr_n = rects[p + 64 + lane];
       }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {

@@ -310,6 +310,17 @@ struct BinBuffers {
   uint32_t* list;        // one entry per instance
   uint2* ranges;         // per tile; those without instances are left as they are
 };
+// The pairs [first, first + n) of segment k of a cell whose pairs are [begin, end):
+// by their number, since first + 2^shift, or a position a step beyond the last
+// pair, may not fit 32 bits (as many pairs as instances, 2^32 - 2 at most).
+struct PairRange {
+  uint32_t first, n;
+};
+__host__ __device__ __forceinline__ PairRange segment_pairs(uint32_t begin, uint32_t end,
+                                                            uint32_t k, uint32_t shift) {
+  const uint32_t first = begin + (k << shift), left = end - first;
+  return {first, left < (1u << shift) ? left : (1u << shift)};
+}
 BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, int32_t n,
                   int tile_w, int tile_h);
 size_t bin_counts_words(const BinPlan& p);
