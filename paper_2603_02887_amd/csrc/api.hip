@@ -622,10 +622,8 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   //    or on the device for a deferred render)
   auto depth_sort = [&](int first) {
     if (in_lds) {
-      launch_depth_local(proj.depth_key, proj.trect, g->n, n_views, P<uint32_t>(ctx->dsort_a),
-                         P<uint32_t>(ctx->slot_a), P<uint32_t>(ctx->dsort_b),
-                         P<uint32_t>(ctx->slot_b), vis, P<uint32_t>(ctx->slot_b),
-                         P<uint2>(ctx->rect_sorted), bins.small, s);
+      launch_depth_local(proj.depth_key, proj.trect, g->n, n_views, vis,
+                         P<uint32_t>(ctx->slot_b), P<uint2>(ctx->rect_sorted), bins.small, s);
       return 1;
     }
     return radix_sort_planned(P<uint32_t>(ctx->depth_key), nullptr, P<uint32_t>(ctx->dsort_a),

@@ -5,8 +5,9 @@
 // equal steps, in no particular order within a bin, and each key then takes its
 // place by comparing itself, and on equal keys its slot, with the few others of
 // its bin.  A crowded bin (many equal or nearly equal depths) would make that
-// quadratic: such a view is sorted through memory by stable passes of up to 8
-// bits (wave matches against per-wave counters).
+// quadratic: such a view is sorted by stable passes of up to 8 bits, in LDS too
+// (8,192 slots on two planes, a 128x128 render: 89 us, with passes through memory
+// 125, with the radix sort 87 to 92; 4,096: 82, 94, 87 to 92).
 // Bound by the latency of its dozen steps: 13.5 us for 4,096 slots, where the
 // radix sort's nine launches took 35 (a 128x128 render of 4,096 Gaussians
 // 112 -> 80 us).  (Larger views dealt to 512 buckets by a sampled table first, and
@@ -21,7 +22,7 @@ namespace {
 constexpr int kNT = 1024;
 constexpr int kDBits = 8;
 constexpr int kDBins = 1 << kDBits;
-constexpr int kSteps = 2048;        // bins of a bucket
+constexpr int kSteps = 2048;        // bins of a view's keys
 constexpr uint32_t kMostInBin = 40; // keys of a bin that are compared with each other
 constexpr uint32_t kCulled = 0xFFFFFFFFu;
 
@@ -34,7 +35,6 @@ struct SortLds {
     uint32_t bin[kSteps];
     __align__(16) uint16_t wave[kWaves][kDBins];
   };
-  uint32_t run[kDBins];
   uint32_t a[kWaves], b[kWaves];
 };
 
@@ -115,11 +115,76 @@ __device__ __forceinline__ void clear_waves(SortLds& S) {
     reinterpret_cast<uint4*>(&S.wave[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// The m <= CAP keys of one work-group, relative to the least (mn; `top` the greatest),
+// by stable passes of up to 8 bits between registers and LDS: wave matches against
+// per-wave counters.  Culled keys are taken as top + 1, and so come last.  Leaves
+// in S.out, in order, where each key lay.
+__device__ void sort_passes(const uint32_t* __restrict__ keys, int m, uint32_t mn, uint32_t top,
+                            SortLds& S) {
+  constexpr int ITEMS = SortLds::CAP / kNT, NW = SortLds::kWaves;
+  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  const int bits = 32 - __clz((int)(top + 1u));
+  const int passes = (bits + kDBits - 1) / kDBits;
+  uint32_t k[ITEMS], v[ITEMS], dig[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int li = wid * (64 * ITEMS) + r * 64 + lane;
+    const uint32_t x = li < m ? keys[li] : kCulled;
+    k[r] = x == kCulled ? top + 1u : x - mn;
+    v[r] = (uint32_t)li;
+  }
+  int shift = 0;
+  for (int p = 0; p < passes; ++p) {
+    const int width = (bits - shift + (passes - p) - 1) / (passes - p);
+    if (p > 0) {
+#pragma unroll
+      for (int r = 0; r < ITEMS; ++r) {
+        const int li = wid * (64 * ITEMS) + r * 64 + lane;
+        k[r] = li < m ? S.key[li] : 0u;
+        v[r] = li < m ? S.idx[li] : 0u;
+      }
+    }
+    clear_waves(S);
+    __syncthreads();
+    wave_ranks<ITEMS>(k, m, shift, width, S, dig, rank);
+    __syncthreads();
+    // each wave's count of a digit becomes its first place
+    {
+      uint32_t c[NW], sum = 0, all;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        c[w] = sum;
+        if (t < kDBins) sum += S.wave[w][t];
+      }
+      const uint32_t ex = block_scan(sum, S.a, &all);
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        if (t < kDBins) S.wave[w][t] = (uint16_t)(ex + c[w]);
+    }
+    __syncthreads();
+    const bool last = p == passes - 1;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const int li = wid * (64 * ITEMS) + r * 64 + lane;
+      if (li < m) {
+        const uint32_t at = S.wave[wid][dig[r]] + rank[r];
+        if (last) {
+          S.out[at] = (uint16_t)v[r];
+        } else {
+          S.key[at] = k[r];
+          S.idx[at] = (uint16_t)v[r];
+        }
+      }
+    }
+    __syncthreads();
+    shift += width;
+  }
+}
+
 // Sorts the m <= CAP keys of one work-group in LDS and leaves in S.out, in order,
-// where each one lay; culled keys are left out.  Returns how many there are, or
-// ~0 if some bin is crowded (nothing is sorted then).  The keys are read from
-// memory (the bucket is in cache after the first time) rather than kept, which
-// leaves registers for all the work-groups LDS has room for.
+// where each one lay; culled keys come after the others or not at all.  Returns
+// how many others there are.  The keys are read from memory again (they are in
+// cache after the first time) rather than kept in registers.
 __device__ uint32_t sort_lds(const uint32_t* __restrict__ keys, int m, SortLds& S) {
   const int t = threadIdx.x;
   for (int i = t; i < kSteps; i += kNT) S.bin[i] = 0u;
@@ -150,7 +215,10 @@ __device__ uint32_t sort_lds(const uint32_t* __restrict__ keys, int m, SortLds& 
     crowded = crowded || c[q] > kMostInBin;
   }
   uint32_t ex = block_scan(sum, S.a, &seen);
-  if (__syncthreads_or(crowded)) return ~0u;
+  if (__syncthreads_or(crowded)) {
+    sort_passes(keys, m, mn, top, S);
+    return seen;
+  }
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     S.bin[kPer * t + q] = ex;
@@ -189,149 +257,20 @@ __device__ __forceinline__ void copy_rect(uint2* __restrict__ to, size_t j,
   else
     to[j] = from[i];
 }
-__device__ __forceinline__ uint2* rect_at(uint2* p, size_t i, bool small) {
-  return small ? reinterpret_cast<uint2*>(reinterpret_cast<uint32_t*>(p) + i) : p + i;
-}
-
-// A bucket through memory (none of its keys culled): passes between
-// (k0, v0), where it lies, and (k1, v1), an even number of them, each counting
-// the whole bucket and then ranking and moving it kNT ITEMS keys at a time.
-template <int ITEMS>
-__device__ void sort_memory(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int m,
-                            const uint2* __restrict__ trect, uint32_t* slots_out,
-                            uint2* __restrict__ rect_out, bool small, SortLds& S) {
-  constexpr int CAP = kNT * ITEMS, NW = kNT / 64;
-  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-  uint32_t mn = kCulled, mx = 0u;
-  for (int i = t; i < m; i += kNT) {
-    mn = min(mn, k0[i]);
-    mx = max(mx, k0[i]);
-  }
-  block_range(mn, mx, S.a, S.b);
-  const uint32_t top = mx - mn;
-  const int bits = top ? 32 - __clz((int)top) : 0;
-  int passes = (bits + kDBits - 1) / kDBits;
-  passes += passes & 1;
-  int shift = 0;
-  uint32_t *ks = k0, *vs = v0, *kd = k1, *vd = v1;
-  for (int p = 0; p < passes; ++p) {
-    const int width = (bits - shift + (passes - p) - 1) / (passes - p);
-    const uint32_t mask = (1u << width) - 1u;
-    __syncthreads();
-    if (t < kDBins) S.run[t] = 0u;
-    __syncthreads();
-    for (int i = t; i < m; i += kNT) atomicAdd(&S.run[((ks[i] - mn) >> shift) & mask], 1u);
-    __syncthreads();
-    {
-      const uint32_t c = t < kDBins ? S.run[t] : 0u;
-      uint32_t all;
-      const uint32_t ex = block_scan(c, S.a, &all);
-      if (t < kDBins) S.run[t] = ex;
-    }
-    for (int c0 = 0; c0 < m; c0 += CAP) {
-      const int cm = min(CAP, m - c0);
-      uint32_t k[ITEMS], v[ITEMS], dig[ITEMS], rank[ITEMS];
-#pragma unroll
-      for (int r = 0; r < ITEMS; ++r) {
-        const int li = wid * (64 * ITEMS) + r * 64 + lane;
-        k[r] = li < cm ? ks[c0 + li] - mn : 0u;
-        v[r] = li < cm ? vs[c0 + li] : 0u;
-      }
-      clear_waves(S);
-      __syncthreads();
-      wave_ranks<ITEMS>(k, cm, shift, width, S, dig, rank);
-      __syncthreads();
-      // (the first position of each wave's digits goes beyond 16 bits: the
-      // digit's running start is kept apart from the wave's place in it)
-      uint32_t start[ITEMS];
-      {
-        uint32_t c[NW], sum = 0;
-        if (t < kDBins) {
-#pragma unroll
-          for (int w = 0; w < NW; ++w) {
-            c[w] = sum;
-            sum += S.wave[w][t];
-          }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) start[r] = S.run[dig[r]];
-        if (t < kDBins) {
-#pragma unroll
-          for (int w = 0; w < NW; ++w) S.wave[w][t] = (uint16_t)c[w];
-        }
-        __syncthreads();
-        if (t < kDBins) S.run[t] += sum;
-      }
-#pragma unroll
-      for (int r = 0; r < ITEMS; ++r) {
-        const int li = wid * (64 * ITEMS) + r * 64 + lane;
-        if (li < cm) {
-          const uint32_t dst = start[r] + S.wave[wid][dig[r]] + rank[r];
-          kd[dst] = k[r] + mn;
-          vd[dst] = v[r];
-        }
-      }
-      __syncthreads();
-    }
-    uint32_t* x = ks;
-    ks = kd;
-    kd = x;
-    x = vs;
-    vs = vd;
-    vd = x;
-    shift += width;
-    __threadfence_block();   // this pass's writes before the next pass reads them
-  }
-  __syncthreads();
-  for (int i = t; i < m; i += kNT) {   // (back in v0)
-    const uint32_t slot = v0[i];
-    slots_out[i] = slot;
-    copy_rect(rect_out, i, trect, slot, small);
-  }
-}
-
-// A view's visible keys and their slots, in slot order, into (key_tmp, slot_tmp);
-// returns how many.
-__device__ uint32_t compact(const uint32_t* __restrict__ keys, uint32_t first, int m,
-                            uint32_t* key_tmp, uint32_t* slot_tmp, uint32_t* s_tmp) {
-  uint32_t done = 0;
-  for (int i0 = 0; i0 < m; i0 += kNT) {
-    const int i = i0 + threadIdx.x;
-    const uint32_t k = i < m ? keys[i] : kCulled;
-    uint32_t all;
-    const uint32_t at = done + block_scan(k != kCulled ? 1u : 0u, s_tmp, &all);
-    if (k != kCulled) {
-      key_tmp[at] = k;
-      slot_tmp[at] = first + (uint32_t)i;
-    }
-    done += all;
-  }
-  __threadfence_block();
-  __syncthreads();
-  return done;
-}
 
 // One work-group per view.
 __global__ __launch_bounds__(kNT) void depth_local_kernel(
-    const uint32_t* __restrict__ depth_key, int32_t n, uint32_t* key_tmp, uint32_t* slot_tmp,
-    uint32_t* key_alt, uint32_t* slot_alt, const uint2* __restrict__ trect,
-    uint32_t* __restrict__ vis, uint32_t* slots_out, uint2* __restrict__ rect_out, bool small) {
+    const uint32_t* __restrict__ depth_key, int32_t n, const uint2* __restrict__ trect,
+    uint32_t* __restrict__ vis, uint32_t* __restrict__ slots_out, uint2* __restrict__ rect_out,
+    bool small) {
   __shared__ SortLds S;
   const size_t base = (size_t)blockIdx.x * (uint32_t)n;
-  const uint32_t* keys = depth_key + base;
-  uint32_t seen = sort_lds(keys, n, S);
-  if (seen != ~0u) {
+  const uint32_t seen = sort_lds(depth_key + base, n, S);
 #pragma unroll 4
-    for (int i = threadIdx.x; i < (int)seen; i += kNT) {
-      const uint32_t slot = (uint32_t)base + S.out[i];
-      slots_out[base + i] = slot;
-      copy_rect(rect_out, base + i, trect, slot, small);
-    }
-  } else {
-    seen = compact(keys, (uint32_t)base, n, key_tmp + base, slot_tmp + base, S.a);
-    sort_memory<4>(key_tmp + base, slot_tmp + base, key_alt + base, slot_alt + base, (int)seen,
-                   trect, slots_out + base, rect_at(rect_out, base, small), small, S);
+  for (int i = threadIdx.x; i < (int)seen; i += kNT) {
+    const uint32_t slot = (uint32_t)base + S.out[i];
+    slots_out[base + i] = slot;
+    copy_rect(rect_out, base + i, trect, slot, small);
   }
   if (threadIdx.x == 0) vis[blockIdx.x] = seen;
 }
@@ -339,12 +278,11 @@ __global__ __launch_bounds__(kNT) void depth_local_kernel(
 }  // namespace
 
 void launch_depth_local(const uint32_t* depth_key, const uint2* trect, int32_t n, int n_views,
-                        uint32_t* key_tmp, uint32_t* slot_tmp, uint32_t* key_alt,
-                        uint32_t* slot_alt, uint32_t* vis, uint32_t* slots_out, uint2* rect_out,
-                        bool small, hipStream_t s) {
+                        uint32_t* vis, uint32_t* slots_out, uint2* rect_out, bool small,
+                        hipStream_t s) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(depth_local_kernel, dim3(n_views), dim3(kNT), 0, s, depth_key, n, key_tmp,
-                     slot_tmp, key_alt, slot_alt, trect, vis, slots_out, rect_out, small);
+  hipLaunchKernelGGL(depth_local_kernel, dim3(n_views), dim3(kNT), 0, s, depth_key, n, trect,
+                     vis, slots_out, rect_out, small);
 }
 
 }  // namespace nxs

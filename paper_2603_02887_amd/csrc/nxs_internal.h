@@ -264,13 +264,11 @@ int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
 
 // Depth sort of views of n <= kLocalMax slots each, one work-group per view
 // (depth.hip), stable: the slots of view v's visible Gaussians and their tile
-// rectangles in order, from v * n on, and vis[v] how many there are.  The
-// temporaries hold a slot each (slot_alt may be slots_out).
+// rectangles in order, from v * n on, and vis[v] how many there are.
 constexpr int kLocalMax = 8192;
 void launch_depth_local(const uint32_t* depth_key, const uint2* trect, int32_t n, int n_views,
-                        uint32_t* key_tmp, uint32_t* slot_tmp, uint32_t* key_alt,
-                        uint32_t* slot_alt, uint32_t* vis, uint32_t* slots_out, uint2* rect_out,
-                        bool small, hipStream_t s);
+                        uint32_t* vis, uint32_t* slots_out, uint2* rect_out, bool small,
+                        hipStream_t s);
 
 // Binning in two levels (bin.hip): each view's slots, in depth order or in slot
 // order (sorted_slots null), are dealt to cells of 2^sx x 2^sy tiles, and each
