@@ -28,6 +28,9 @@ namespace {
 // NXS_SORT_AUTO takes the tile-first order up to this many expected
 // instances per tile on average (0: never)
 constexpr double kAutoTileFirstPerTile = 0.0;
+// slots, and expected instances, up to which a render of few tiles emits its
+// instances (see forward())
+constexpr int64_t kEmitMost = int64_t(1) << 20;
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -473,9 +476,36 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     grid_xy[n_views + v] = (cams[v].height + th - 1) / th;
   }
   const BinPlan bins = plan_bins(grid_xy.data(), grid_xy.data() + n_views, n_views, g->n, tw, th);
-  const bool by_cell = bins.n_cells > 0;
-  const uint32_t slot_mask = by_cell && bins.pack ? kPackMask : ~0u;
-  const int ax = by_cell ? bins.ax : 0, ay = by_cell ? bins.ay : 0;
+  // a deferred render needs instance buffers sized by an earlier render;
+  // until then it waits for the count like any other
+  const bool deferred = c.deferred && !ctx->noalloc && instance_capacity(ctx) > 0;
+  // (the count of the latest deferred render whose status has landed)
+  if (deferred && ctx->host_status->last) ctx->m_hint = ctx->host_status->last;
+  // the list order: the caller's, else by the expected instances per tile
+  // (the hint, else the context's last count; unknown: depth first)
+  const double expect_m = opts->instance_hint > 0.0f ? (double)opts->instance_hint
+                                                     : (double)ctx->m_hint;
+  bool tile_first = c.sort_order == NXS_SORT_TILE_FIRST;
+  if (c.sort_order == NXS_SORT_AUTO)
+    tile_first = expect_m > 0.0 && expect_m <= kAutoTileFirstPerTile * (double)total_tiles;
+  // Small views are sorted by depth in LDS, and binned in two levels.  Otherwise
+  // a render of few tiles has its instances emitted and sorted by tile, where
+  // that takes one radix pass: six launches against seven, and fewer steps in
+  // each (one view of 160x196, 257k Gaussians, 182 us against 193; 400x300, 100k, 113
+  // against 121; 128x128, 400k, 424 against 445).  Beyond 512 tiles it takes two
+  // passes, and loses (640x200, 520 tiles, 100k: 115 against 111); so it does for
+  // many slots (four views of 600k, 484 against 425) and many instances a slot
+  // (1024x128, 200k of 1.9M, 147 against 117), whose number is only known from
+  // an earlier render (not asked where memory is limited: a context then keeps
+  // to one way).
+  const bool in_lds = bins.n_cells > 0 && !tile_first && g->n > 0 && g->n <= kLocalMax;
+  const bool many = !ctx->noalloc && !ctx->ws_limit && expect_m > (double)kEmitMost &&
+                    expect_m > 2.5 * (double)S;
+  const bool few_tiles = total_tiles <= (1 << kMaxDigitBits) && S <= kEmitMost && !many;
+  const bool by_cell = bins.n_cells > 0 && (in_lds || !few_tiles);
+  const bool small = by_cell && bins.small;
+  const uint32_t slot_mask = bins.pack ? kPackMask : ~0u;
+  const int ax = bins.ax, ay = bins.ay;
   const int sort_parts = by_cell ? n_views : 1;   // each view's slots on their own
   int64_t off = 0, pix_off = 0, cell_off = 0;
   for (int v = 0; v < n_views; ++v) {
@@ -502,9 +532,6 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     pix_off += (int64_t)cm.width * cm.height;
     d.rgb = out[v].rgb; d.trans = out[v].trans; d.od = out[v].overdraw;
   }
-  // a deferred render needs instance buffers sized by an earlier render;
-  // until then it waits for the count like any other
-  const bool deferred = c.deferred && !ctx->noalloc && instance_capacity(ctx) > 0;
   DoneGuard guard{ctx, s};
   nxs_status st;
   if ((st = ensure(ctx, ctx->views, sizeof(ViewDev) * n_views, s))) return st;
@@ -526,12 +553,12 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   if ((st = ensure(ctx, ctx->depth_key, 4 * S, s)) || (st = ensure(ctx, ctx->dsort_a, 4 * S, s)) ||
       (st = ensure(ctx, ctx->dsort_b, 4 * S, s)) ||
       (st = ensure(ctx, ctx->slot_a, 4 * S, s)) || (st = ensure(ctx, ctx->slot_b, 4 * S, s)) ||
-      (st = ensure(ctx, ctx->trect, (bins.small ? 4 : 8) * S, s)) ||
-      (st = ensure(ctx, ctx->rect_sorted, (bins.small ? 4 : 8) * S, s)) ||
+      (st = ensure(ctx, ctx->trect, (small ? 4 : 8) * S, s)) ||
+      (st = ensure(ctx, ctx->rect_sorted, (small ? 4 : 8) * S, s)) ||
       (st = ensure(ctx, ctx->prec, 48 * S, s)) ||
       (st = ensure(ctx, ctx->counts,
                    4 * std::max(radix_counts_words(S / sort_parts, sort_parts),
-                                bin_counts_words(bins)),
+                                by_cell ? bin_counts_words(bins) : 0),
                    s)) ||
       (st = ensure(ctx, ctx->ranges, 8 * total_tiles + 4 * kSchedCounters, s)))
     return st;
@@ -550,13 +577,11 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
       ctx->status_clear = true;
     }
     icap = instance_capacity(ctx);
-    // (the count of the latest deferred render whose status has landed)
-    if (ctx->host_status->last) ctx->m_hint = ctx->host_status->last;
     if (!by_cell &&
         (st = ensure(ctx, ctx->counts, 4 * radix_counts_words(std::max<int64_t>(S, icap)), s)))
       return st;
   }
-  ProjDev proj{P<uint32_t>(ctx->depth_key), P<uint2>(ctx->trect), bins.small,
+  ProjDev proj{P<uint32_t>(ctx->depth_key), P<uint2>(ctx->trect), small,
                P<float4>(ctx->prec)};
   GaussDev gd{g->means, g->scales, g->quats, g->opacities, g->sh, g->n, g->sh_degree};
   Counters* dcount = P<Counters>(ctx->counters);
@@ -566,17 +591,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   };
   ctx->ev_valid = false;
   HIP_TRY(mark(0));
-  // the list order: the caller's, else by the expected instances per tile
-  // (the hint, else the context's last count; unknown: depth first)
-  bool tile_first = c.sort_order == NXS_SORT_TILE_FIRST;
-  if (c.sort_order == NXS_SORT_AUTO) {
-    const double expect = opts->instance_hint > 0.0f ? (double)opts->instance_hint
-                                                     : (double)ctx->m_hint;
-    tile_first = expect > 0.0 && expect <= kAutoTileFirstPerTile * (double)total_tiles;
-  }
-  // small views are sorted by depth in LDS; vis: visible slots per view, the
-  // only ones sorted then
-  const bool in_lds = by_cell && !tile_first && g->n > 0 && g->n <= kLocalMax;
+  // the visible slots per view, the only ones that are sorted in LDS
   uint32_t* vis = nullptr;
   if (in_lds) {
     if ((st = ensure(ctx, ctx->vis, 4 * (size_t)n_views, s))) return st;
@@ -623,7 +638,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   auto depth_sort = [&](int first) {
     if (in_lds) {
       launch_depth_local(proj.depth_key, proj.trect, g->n, n_views, vis,
-                         P<uint32_t>(ctx->slot_b), P<uint2>(ctx->rect_sorted), bins.small, s);
+                         P<uint32_t>(ctx->slot_b), P<uint2>(ctx->rect_sorted), small, s);
       return 1;
     }
     return radix_sort_planned(P<uint32_t>(ctx->depth_key), nullptr, P<uint32_t>(ctx->dsort_a),
@@ -632,7 +647,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
                               dcount->plan, first,
                               P<uint32_t>(ctx->counts), proj.trect,
                               by_cell ? nullptr : P<uint32_t>(ctx->nt_sorted),
-                              P<uint2>(ctx->rect_sorted), bins.small, s);
+                              P<uint2>(ctx->rect_sorted), small, ax, ay, s);
   };
   // (tile first: no depth sort; the slots are binned in their own order)
   uint32_t* sorted_slots = nullptr;
@@ -643,15 +658,15 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   const uint2* rects = tile_first ? proj.trect : P<uint2>(ctx->rect_sorted);
   HIP_TRY(mark(3));
   // 2. binning (in depth order, or in slot order): the slots' cells counted and,
-  //    with the buffers as they are, dealt to the cells; or, for very many
-  //    cells, every instance emitted
+  //    with the buffers as they are, dealt to the cells; or, for few tiles or
+  //    very many cells, every instance emitted
   BinBuffers bb{P<uint32_t>(ctx->counts), P<uint32_t>(ctx->cells), nullptr, nullptr, nullptr,
                 nullptr, P<uint2>(ctx->ranges)};
   auto count_slots = [&]() {
     if (by_cell)
       launch_bin_count(bins, bb, rects, vis, dviews, dcount, s);
     else
-      launch_emit_scan(tile_first ? nullptr : P<uint32_t>(ctx->nt_sorted), proj.trect, S,
+      launch_emit_scan(tile_first ? nullptr : P<uint32_t>(ctx->nt_sorted), proj.trect, ax, ay, S,
                        P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums), s);
   };
   auto write_slots = [&](uint64_t cap) {
@@ -660,10 +675,10 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
       bb.pair_rect = P<uint16_t>(ctx->inst_tile_alt);
       launch_bin_scatter(bins, bb, sorted_slots, rects, vis, dviews, cap, dcount, s);
     } else {
-      launch_emit_write(sorted_slots, tile_first ? nullptr : rects, proj.trect, S, g->n, dviews,
-                        P<uint32_t>(ctx->scan_local), P<uint32_t>(ctx->block_sums),
-                        (uint32_t)cap, P<uint32_t>(ctx->inst_tile), P<uint32_t>(ctx->inst_val),
-                        s);
+      launch_emit_write(sorted_slots, tile_first ? nullptr : rects, proj.trect, ax, ay, ~slot_mask,
+                        S, g->n, dviews, P<uint32_t>(ctx->scan_local),
+                        P<uint32_t>(ctx->block_sums), (uint32_t)cap, P<uint32_t>(ctx->inst_tile),
+                        P<uint32_t>(ctx->inst_val), s);
     }
   };
   count_slots();
@@ -797,7 +812,7 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   ctx->last_ax = ax;
   ctx->last_ay = ay;
   ctx->last_slot_mask = slot_mask;
-  ctx->last_small = bins.small;
+  ctx->last_small = small;
 
   if (state_out) {
     // hand the buffers the backward re-reads to a new state; the context

@@ -41,9 +41,9 @@ struct GaussDev {
 // Per projected slot (slot = view * n + gaussian) arrays written by the projection.
 struct ProjDev {
   uint32_t* depth_key;      // float32 depth bits; 0xFFFFFFFF when culled
-  // rectangle (x0 | x1 << 16, y0 | y1 << 16), all ones when culled: in blocks
-  // of 8x8 pixels for the two-level binning (the tiles it covers are
-  // tile_rect() of it), else in tiles; `small`: as small_rect() words
+  // rectangle (x0 | x1 << 16, y0 | y1 << 16) in blocks of 8x8 pixels, all ones
+  // when culled (the tiles it covers are tile_rect() of it); `small`: as
+  // small_rect() words
   uint2* trect;
   bool small;
   // 3 float4 per slot:
@@ -255,12 +255,13 @@ int radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
 // with first_pass = 0 otherwise).  The result is in (k1, v1); returns 1.
 // The last pass also writes, in sorted order, each value's tile rectangle
 // from `trect` (indexed by value; both arrays of small_rect() words if `small`)
-// into rect_out, and its tile count into nt_out unless that is null.
+// into rect_out, and its tile count (tiles of 2^ax x 2^ay units) into nt_out unless
+// that is null.
 int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0,
                        uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int parts,
                        const uint32_t* plan, int first_pass, uint32_t* counts,
-                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small,
-                       hipStream_t s);
+                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small, int ax,
+                       int ay, hipStream_t s);
 
 // Depth sort of views of n <= kLocalMax slots each, one work-group per view
 // (depth.hip), stable: the slots of view v's visible Gaussians and their tile
@@ -339,21 +340,22 @@ void launch_bin_tiles(const BinPlan& p, const BinBuffers& b, uint64_t m_plan,
                       const ViewDev* views, const Counters* counters, hipStream_t s);
 
 // Renders the two-level binning does not apply to emit every instance and sort
-// them all by tile instead:
+// them all by tile instead (the list entries are the same, pack_mask 0 or
+// ~kPackMask; tiles are 2^ax x 2^ay of the rectangles' blocks):
 // exclusive scan of ntiles in sorted-slot order and emission of instances.
 size_t scan_blocks_size(int64_t n);
 // Exclusive scan of the depth-sorted tile counts (nt_sorted), or with
 // nt_sorted null of the tile counts of the rectangles in slot order, per block
 // of 512 slots (block totals in block_sums; scanned across blocks here
 // only when there are more blocks than the emission sums itself).
-void launch_emit_scan(const uint32_t* nt_sorted, const uint2* trect, int64_t n_slots,
-                      uint32_t* scan_local, uint32_t* block_sums, hipStream_t s);
+void launch_emit_scan(const uint32_t* nt_sorted, const uint2* trect, int ax, int ay,
+                      int64_t n_slots, uint32_t* scan_local, uint32_t* block_sums, hipStream_t s);
 // Writes the instances of the depth-sorted slots (rectangles in
 // rect_sorted), or with sorted_slots null of the slots in their own order
 // (rectangles in trect); instances at positions >= capacity are not written.
 void launch_emit_write(const uint32_t* sorted_slots, const uint2* rect_sorted,
-                       const uint2* trect, int64_t n_slots, int32_t n_gauss,
-                       const ViewDev* views, const uint32_t* scan_local,
+                       const uint2* trect, int ax, int ay, uint32_t pack_mask, int64_t n_slots,
+                       int32_t n_gauss, const ViewDev* views, const uint32_t* scan_local,
                        const uint32_t* block_sums, uint32_t capacity, uint32_t* inst_tile,
                        uint32_t* inst_val, hipStream_t s);
 

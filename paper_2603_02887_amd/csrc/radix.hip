@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
     const uint32_t* __restrict__ plan, int pass, uint32_t parts, uint32_t cpp, uint32_t per,
     const uint32_t* __restrict__ counts, const uint32_t* __restrict__ totals,
     const uint2* __restrict__ trect, uint32_t* __restrict__ nt_out,
-    uint2* __restrict__ rect_out, const Counters* __restrict__ dn) {
+    uint2* __restrict__ rect_out, int ax, int ay, const Counters* __restrict__ dn) {
   // Per-wave digit counts (at most 64 * ITEMS), then each wave's first
   // position per digit in the chunk (below 256 * ITEMS), are kept in 16 bits:
   // at 4,096 keys the tables then leave room for four work-groups per CU.
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kRThreads) void rx_scatter(
                 reinterpret_cast<const uint32_t*>(trect)[v];
           } else {
             const uint2 rc = trect[v];
-            if (nt_out) nt_out[g] = rect_tile_count(rc);
+            if (nt_out) nt_out[g] = rect_tile_count(tile_rect(rc, ax, ay));
             rect_out[g] = rc;
           }
         }
@@ -757,8 +757,8 @@ namespace {
 int run_passes(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, uint32_t* v0,
                uint32_t* k1, uint32_t* v1, int64_t n, int first, int passes,
                const int* shifts, const int* widths, const uint32_t* plan, uint32_t* counts,
-               const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small, hipStream_t s,
-               const Counters* dn, int64_t n_plan, int parts = 1) {
+               const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small, int ax, int ay,
+               hipStream_t s, const Counters* dn, int64_t n_plan, int parts = 1) {
   // n (per part) bounds the keys (the counts layout); the grid is planned for n_plan
   // keys (with dn, the count expected on the device) and loops beyond it
   const bool large = n_plan * parts >= kRLargeFrom;
@@ -784,7 +784,7 @@ int run_passes(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
                          plan, p, n, dn);
       hipLaunchKernelGGL(scatter, dim3(grid), dim3(kRThreads), 0, s, kin, vin, keys_in, vals_in,
                          kout, vout, n, shift, width, plan, p, (uint32_t)parts, nchunks, per,
-                         counts, totals, last ? trect : nullptr, nt_out, rect_out, dn);
+                         counts, totals, last ? trect : nullptr, nt_out, rect_out, ax, ay, dn);
     };
     if (large)
       pass(rx_count<kRItemsLarge>, rx_scan<kRItemsLarge>,
@@ -813,18 +813,19 @@ int radix_sort(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0, u
     shift += widths[p];
   }
   return run_passes(keys_in, vals_in, k0, v0, k1, v1, n, 0, passes, shifts, widths, nullptr,
-                    counts, nullptr, nullptr, nullptr, false, s, dn,
+                    counts, nullptr, nullptr, nullptr, false, 0, 0, s, dn,
                     dn && n_plan > 0 ? std::min(n_plan, n) : n);
 }
 
 int radix_sort_planned(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* k0,
                        uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int parts,
                        const uint32_t* plan, int first_pass, uint32_t* counts,
-                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small,
-                       hipStream_t s) {
+                       const uint2* trect, uint32_t* nt_out, uint2* rect_out, bool small, int ax,
+                       int ay, hipStream_t s) {
   if (n <= 0) return 1;
   return run_passes(keys_in, vals_in, k0, v0, k1, v1, n, first_pass, kPlanPasses, nullptr,
-                    nullptr, plan, counts, trect, nt_out, rect_out, small, s, nullptr, n, parts);
+                    nullptr, plan, counts, trect, nt_out, rect_out, small, ax, ay, s, nullptr, n,
+                    parts);
 }
 
 void launch_tile_depth_sort(const uint2* ranges, int64_t n_tiles, const uint32_t* depth_key,

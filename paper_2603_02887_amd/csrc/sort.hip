@@ -50,15 +50,15 @@ constexpr int kScanChunk = kScanBlock * kScanItems;
 // depth-sorted order, or (nt_sorted null) the counts in the projection's
 // rectangles, in slot order.
 __global__ __launch_bounds__(kScanBlock) void scan_local_kernel(
-    const uint32_t* __restrict__ nt_sorted, const uint2* __restrict__ trect, int64_t n,
-    uint32_t* __restrict__ local, uint32_t* __restrict__ block_sums) {
+    const uint32_t* __restrict__ nt_sorted, const uint2* __restrict__ trect, int ax, int ay,
+    int64_t n, uint32_t* __restrict__ local, uint32_t* __restrict__ block_sums) {
   __shared__ uint32_t s_tmp[kScanBlock / 64];
   const int64_t base = (int64_t)blockIdx.x * kScanChunk + threadIdx.x * kScanItems;
   uint32_t v[kScanItems], sum = 0;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     int64_t i = base + k;
-    v[k] = i < n ? (nt_sorted ? nt_sorted[i] : rect_tile_count(trect[i])) : 0u;
+    v[k] = i < n ? (nt_sorted ? nt_sorted[i] : rect_tile_count(tile_rect(trect[i], ax, ay))) : 0u;
     sum += v[k];
   }
   uint32_t tot;
@@ -117,11 +117,18 @@ __global__ __launch_bounds__(kSumThreads) void scan_blocks_kernel(uint32_t* __re
 constexpr int kInlineBlocks = 2048;
 constexpr uint32_t kEmitWindow = 4096;   // positions per owner map (8 KB)
 constexpr uint32_t kEmitShort = 32;      // longer runs are marked by a whole wave
+// Beside them, kEmitExtra work-groups take the windows beyond the first of every
+// block's run: in depth order the nearest slots, which cover the most tiles, share a
+// block, and one work-group for its run was the kernel's time (with the camera among
+// 50,000 Gaussians, 256x256, M = 0.9M: the render 485 us then, 106 now).
+constexpr int kEmitExtra = 256;
 
-// sorted_slots null: the slots in their own order, rectangles from trect.
+// sorted_slots null: the slots in their own order, rectangles from trect.  An
+// entry's bits above its slot, where pack_mask keeps them, are the 8x8 blocks of
+// the tile that the slot's rectangle covers (row by row).
 __global__ __launch_bounds__(kScanBlock) void emit_kernel(
     const uint32_t* __restrict__ sorted_slots, const uint2* __restrict__ rect_sorted,
-    const uint2* __restrict__ trect, int64_t n,
+    const uint2* __restrict__ trect, int ax, int ay, uint32_t pack_mask, int64_t n,
     int32_t n_gauss, int n_views, const ViewDev* __restrict__ views,
     const uint32_t* __restrict__ local, const uint32_t* __restrict__ block_sums, int nblocks,
     uint32_t capacity, uint32_t* __restrict__ inst_tile, uint32_t* __restrict__ inst_val) {
@@ -129,131 +136,182 @@ __global__ __launch_bounds__(kScanBlock) void emit_kernel(
   __shared__ uint32_t s_slot[kScanChunk];
   __shared__ uint32_t s_tile0[kScanChunk];   // global tile of the rectangle's first tile
   __shared__ uint32_t s_geom[kScanChunk];    // width | tiles_x << 16
+  // the rectangle's blocks from its first tile's corner (x0 | x1 << 16, y0 | y1 << 16)
+  __shared__ uint2 s_blocks[kScanChunk];
   __shared__ uint32_t s_tmp[kScanBlock / 64];
   __shared__ uint16_t s_owner[kEmitWindow];   // block-local slot of each position
-  const int64_t b0 = (int64_t)blockIdx.x * kScanChunk;
-  const int cnt = (int)min((int64_t)kScanChunk, n - b0);
+  __shared__ uint32_t s_find[2];
   // This block's output offset: with the inline sum (many loads and a block
   // scan) before the slots' loads, else after them (measured both ways: the
   // 1080p frame's 1,954 blocks 20.9 against 21.8 us with the sum first; the
   // eight 720p views' 7,813 pre-scanned blocks 149 against 154 us with the
   // loads first).
   const bool inline_sum = nblocks <= kInlineBlocks;
-  uint32_t out0 = 0, out1 = 0;
-  auto block_offset = [&]() {
-    if (inline_sum) {
-      // the sum of the totals of the blocks before this one (all of a
-      // thread's loads issued before the first is added)
-      constexpr int kInlinePerT = kInlineBlocks / kScanBlock;
-      static_assert(kInlineBlocks % kScanBlock == 0, "whole rounds of block totals");
-      uint32_t v[kInlinePerT];
+  constexpr int kInlinePerT = kInlineBlocks / kScanBlock;
+  static_assert(kInlineBlocks % kScanBlock == 0, "whole rounds of block totals");
+  uint32_t totals[kInlinePerT];   // (all of a thread's loads issued together)
+  if (inline_sum) {
 #pragma unroll
-      for (int q = 0; q < kInlinePerT; ++q) {
-        const int b = q * kScanBlock + threadIdx.x;
-        v[q] = b < (int)blockIdx.x ? block_sums[b] : 0u;
+    for (int q = 0; q < kInlinePerT; ++q) {
+      const int b = q * kScanBlock + threadIdx.x;
+      totals[q] = b < nblocks ? block_sums[b] : 0u;
+    }
+  }
+  // block `blk`'s windows from w0 on that begin before `end`
+  auto emit = [&](int blk, uint32_t w0, uint32_t end) {
+    const int64_t b0 = (int64_t)blk * kScanChunk;
+    const int cnt = (int)min((int64_t)kScanChunk, n - b0);
+    uint32_t out0 = 0;
+    auto block_offset = [&]() {
+      if (inline_sum) {   // the sum of the totals of the blocks before this one
+        uint32_t part = 0;
+#pragma unroll
+        for (int q = 0; q < kInlinePerT; ++q)
+          part += q * kScanBlock + (int)threadIdx.x < blk ? totals[q] : 0u;
+        uint32_t all;
+        (void)block_exclusive_scan(part, s_tmp, &all);
+        out0 = all;
+      } else {
+        out0 = block_sums[blk];   // scanned in place
       }
-      uint32_t part = 0;
-#pragma unroll
-      for (int q = 0; q < kInlinePerT; ++q) part += v[q];
-      uint32_t all;
-      (void)block_exclusive_scan(part, s_tmp, &all);
-      out0 = all;
-      out1 = out0 + block_sums[blockIdx.x];
-    } else {
-      out0 = block_sums[blockIdx.x];   // scanned in place
-      out1 = out0 + block_sums[nblocks + blockIdx.x];
-    }
-  };
-  if (inline_sum) block_offset();
-  // the slots' loads (all independent), then the LDS tables
-  constexpr int kPerT = kScanChunk / kScanBlock;
-  uint32_t slot_r[kPerT], off_r[kPerT];
-  uint2 rect_r[kPerT];
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int k = q * kScanBlock + threadIdx.x;
-    slot_r[q] = k < cnt ? (sorted_slots ? sorted_slots[b0 + k] : (uint32_t)(b0 + k)) : 0u;
-    off_r[q] = k < cnt ? local[b0 + k] : 0u;
-  }
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int k = q * kScanBlock + threadIdx.x;
-    if (k >= cnt) {
-      rect_r[q] = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
-    } else if (sorted_slots) {
-      rect_r[q] = rect_sorted[b0 + k];
-    } else {
-      rect_r[q] = trect[b0 + k];
-    }
-  }
-  if (!inline_sum) block_offset();
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int k = q * kScanBlock + threadIdx.x;
-    if (k >= cnt) continue;
-    s_slot[k] = slot_r[q];
-    s_off[k] = off_r[q];
-    const uint2 r = rect_r[q];
-    if (r.x != 0xFFFFFFFFu) {
-      const uint32_t vi = n_views == 1 ? 0u : slot_r[q] / (uint32_t)n_gauss;
-      const uint32_t tile_off = (uint32_t)views[vi].tile_off;
-      const uint32_t tiles_x = (uint32_t)views[vi].tiles_x;
-      const uint32_t tx0 = r.x & 0xFFFF, tx1 = r.x >> 16, ty0 = r.y & 0xFFFF;
-      s_tile0[k] = tile_off + ty0 * tiles_x + tx0;
-      s_geom[k] = (tx1 - tx0 + 1) | (tiles_x << 16);
-    } else {
-      s_tile0[k] = 0;
-      s_geom[k] = 1;
-    }
-  }
-  __syncthreads();
-  const uint32_t tot = out1 - out0;
-  // slot k owns positions [s_off[k], s_off[k + 1]) (the last one: up to tot)
-  const int lane = threadIdx.x & 63;
-  uint32_t end_r[kPerT];
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int k = q * kScanBlock + threadIdx.x;
-    end_r[q] = k + 1 < cnt ? s_off[k + 1] : (k < cnt ? tot : off_r[q]);
-  }
-  for (uint32_t w0 = 0; w0 < tot; w0 += kEmitWindow) {
-    const uint32_t w1 = min(tot, w0 + kEmitWindow);
-    // a short run is marked by its slot's thread, a long one by the whole
-    // wave (the slot's lane broadcasts its bounds)
+    };
+    const uint32_t tot = block_sums[nblocks + blk];
+    end = min(end, tot);
+    if (inline_sum) block_offset();
+    // the slots' loads (all independent), then the LDS tables
+    constexpr int kPerT = kScanChunk / kScanBlock;
+    uint32_t slot_r[kPerT], off_r[kPerT];
+    uint2 rect_r[kPerT];
 #pragma unroll
     for (int q = 0; q < kPerT; ++q) {
       const int k = q * kScanBlock + threadIdx.x;
-      const uint32_t a = off_r[q], e = end_r[q];
-      const bool longrun = e - a > kEmitShort;
-      if (!longrun)
-        for (uint32_t j = max(a, w0); j < min(e, w1); ++j) s_owner[j - w0] = (uint16_t)k;
-      uint64_t runs = __ballot(longrun);
-      while (runs) {
-        const int b = __builtin_ctzll(runs);
-        runs &= runs - 1;
-        // (b is the same on every lane: the bounds come by readlane)
-        const uint32_t ba = (uint32_t)__builtin_amdgcn_readlane((int)a, b);
-        const uint32_t be = (uint32_t)__builtin_amdgcn_readlane((int)e, b);
-        const uint16_t bk = (uint16_t)(k - lane + b);
-        for (uint32_t j = max(ba, w0) + lane; j < min(be, w1); j += 64) s_owner[j - w0] = bk;
+      slot_r[q] = k < cnt ? (sorted_slots ? sorted_slots[b0 + k] : (uint32_t)(b0 + k)) : 0u;
+      off_r[q] = k < cnt ? local[b0 + k] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int k = q * kScanBlock + threadIdx.x;
+      if (k >= cnt) {
+        rect_r[q] = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
+      } else if (sorted_slots) {
+        rect_r[q] = rect_sorted[b0 + k];
+      } else {
+        rect_r[q] = trect[b0 + k];
+      }
+    }
+    if (!inline_sum) block_offset();
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int k = q * kScanBlock + threadIdx.x;
+      if (k >= cnt) continue;
+      s_slot[k] = slot_r[q];
+      s_off[k] = off_r[q];
+      const uint2 r = tile_rect(rect_r[q], ax, ay);
+      if (r.x != 0xFFFFFFFFu) {
+        const uint32_t vi = n_views == 1 ? 0u : slot_r[q] / (uint32_t)n_gauss;
+        const uint32_t tile_off = (uint32_t)views[vi].tile_off;
+        const uint32_t tiles_x = (uint32_t)views[vi].tiles_x;
+        const uint32_t tx0 = r.x & 0xFFFF, tx1 = r.x >> 16, ty0 = r.y & 0xFFFF;
+        s_tile0[k] = tile_off + ty0 * tiles_x + tx0;
+        s_geom[k] = (tx1 - tx0 + 1) | (tiles_x << 16);
+        const uint32_t ox = tx0 << ax, oy = ty0 << ay;
+        s_blocks[k] = make_uint2(rect_r[q].x - (ox | ox << 16), rect_r[q].y - (oy | oy << 16));
+      } else {
+        s_tile0[k] = 0;
+        s_geom[k] = 1;
       }
     }
     __syncthreads();
-    for (uint32_t q = w0 + threadIdx.x; q < w1; q += kScanBlock) {
-      const int k = s_owner[q - w0];
-      const uint32_t geom = s_geom[k];
-      const uint32_t w = geom & 0xFFFF, tiles_x = geom >> 16;
-      const uint32_t l = q - s_off[k];
-      // row = l / w in float (exact for l < 2^24 after the +-1 fix-up)
-      uint32_t row = (uint32_t)((float)l * __frcp_rn((float)w));
-      if (row * w > l) --row;
-      if ((row + 1) * w <= l) ++row;
-      if (out0 + q < capacity) {
-        inst_tile[out0 + q] = s_tile0[k] + row * tiles_x + (l - row * w);
-        inst_val[out0 + q] = s_slot[k];
+    // slot k owns positions [s_off[k], s_off[k + 1]) (the last one: up to tot)
+    const int lane = threadIdx.x & 63;
+    uint32_t end_r[kPerT];
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int k = q * kScanBlock + threadIdx.x;
+      end_r[q] = k + 1 < cnt ? s_off[k + 1] : (k < cnt ? tot : off_r[q]);
+    }
+    for (; w0 < end; w0 += kEmitWindow) {
+      const uint32_t w1 = min(tot, w0 + kEmitWindow);
+      // a short run is marked by its slot's thread, a long one by the whole
+      // wave (the slot's lane broadcasts its bounds)
+#pragma unroll
+      for (int q = 0; q < kPerT; ++q) {
+        const int k = q * kScanBlock + threadIdx.x;
+        const uint32_t a = off_r[q], e = end_r[q];
+        const bool longrun = e - a > kEmitShort;
+        if (!longrun)
+          for (uint32_t j = max(a, w0); j < min(e, w1); ++j) s_owner[j - w0] = (uint16_t)k;
+        uint64_t runs = __ballot(longrun);
+        while (runs) {
+          const int b = __builtin_ctzll(runs);
+          runs &= runs - 1;
+          // (b is the same on every lane: the bounds come by readlane)
+          const uint32_t ba = (uint32_t)__builtin_amdgcn_readlane((int)a, b);
+          const uint32_t be = (uint32_t)__builtin_amdgcn_readlane((int)e, b);
+          const uint16_t bk = (uint16_t)(k - lane + b);
+          for (uint32_t j = max(ba, w0) + lane; j < min(be, w1); j += 64) s_owner[j - w0] = bk;
+        }
+      }
+      __syncthreads();
+      for (uint32_t q = w0 + threadIdx.x; q < w1; q += kScanBlock) {
+        const int k = s_owner[q - w0];
+        const uint32_t geom = s_geom[k];
+        const uint32_t w = geom & 0xFFFF, tiles_x = geom >> 16;
+        const uint32_t l = q - s_off[k];
+        // row = l / w in float (exact for l < 2^24 after the +-1 fix-up)
+        uint32_t row = (uint32_t)((float)l * __frcp_rn((float)w));
+        if (row * w > l) --row;
+        if ((row + 1) * w <= l) ++row;
+        const uint32_t col = l - row * w;
+        // the covered blocks of tile (col, row): its columns, once per covered row
+        const uint2 bl = s_blocks[k];
+        const int nx = 1 << ax, ny = 1 << ay;
+        const int x0 = max((int)(bl.x & 0xFFFF) - (int)(col << ax), 0);
+        const int x1 = min((int)(bl.x >> 16) - (int)(col << ax), nx - 1);
+        const int y0 = max((int)(bl.y & 0xFFFF) - (int)(row << ay), 0);
+        const int y1 = min((int)(bl.y >> 16) - (int)(row << ay), ny - 1);
+        const uint32_t cols = (2u << x1) - (1u << x0);
+        const uint32_t blocks = (y0 == 0 ? cols : 0u) | (y1 > 0 ? cols << nx : 0u);
+        if (out0 + q < capacity) {
+          inst_tile[out0 + q] = s_tile0[k] + row * tiles_x + col;
+          inst_val[out0 + q] = s_slot[k] | ((blocks << 28) & pack_mask);
+        }
+      }
+      __syncthreads();   // the next window's marks overwrite this one's
+    }
+  };
+  const bool own = (int)blockIdx.x < nblocks;   // else: one of the extra work-groups
+  const uint32_t extra = gridDim.x - nblocks;
+  uint32_t first = 0, mine = 0, all = 1;
+  auto beyond = [](uint32_t t) { return t ? (t - 1u) / kEmitWindow : 0u; };
+  if (!own) {
+    // all the windows beyond their block's first, in the order of the threads
+    // that hold the blocks' totals: this thread's are [first, first + mine)
+#pragma unroll
+    for (int q = 0; q < kInlinePerT; ++q) mine += beyond(totals[q]);
+    first = block_exclusive_scan(mine, s_tmp, &all);
+  }
+  // (every thread of the work-group takes the same steps)
+  for (uint32_t j = own ? 0u : blockIdx.x - nblocks; j < all; j += own ? 1u : extra) {
+    if (!own && j >= first && j < first + mine) {
+      uint32_t k = j - first;
+      bool found = false;
+#pragma unroll
+      for (int q = 0; q < kInlinePerT; ++q) {
+        const uint32_t o = beyond(totals[q]);
+        if (!found && k < o) {
+          s_find[0] = q * kScanBlock + threadIdx.x;
+          s_find[1] = (k + 1u) * kEmitWindow;
+          found = true;
+        }
+        k -= found ? 0u : o;
       }
     }
-    __syncthreads();   // the next window's marks overwrite this one's
+    __syncthreads();
+    const int blk = own ? (int)blockIdx.x : (int)s_find[0];
+    const uint32_t w0 = own ? 0u : s_find[1];
+    emit(blk, w0, extra ? w0 + kEmitWindow : 0xFFFFFFFFu);
+    __syncthreads();   // (s_find and the tables are free again)
   }
 }
 
@@ -321,28 +379,29 @@ size_t scan_blocks_size(int64_t n) {
   return 2 * (size_t)((n + kScanChunk - 1) / kScanChunk) + 1;
 }
 
-void launch_emit_scan(const uint32_t* nt_sorted, const uint2* trect, int64_t n_slots,
-                      uint32_t* scan_local, uint32_t* block_sums, hipStream_t s) {
+void launch_emit_scan(const uint32_t* nt_sorted, const uint2* trect, int ax, int ay,
+                      int64_t n_slots, uint32_t* scan_local, uint32_t* block_sums, hipStream_t s) {
   if (n_slots <= 0) return;
   const int nblocks = (int)((n_slots + kScanChunk - 1) / kScanChunk);
   hipLaunchKernelGGL(scan_local_kernel, dim3(nblocks), dim3(kScanBlock), 0, s, nt_sorted, trect,
-                     n_slots, scan_local, block_sums);
+                     ax, ay, n_slots, scan_local, block_sums);
   if (nblocks > kInlineBlocks)
     hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(kSumThreads), 0, s, block_sums,
                        nblocks);
 }
 
 void launch_emit_write(const uint32_t* sorted_slots, const uint2* rect_sorted,
-                       const uint2* trect, int64_t n_slots, int32_t n_gauss,
-                       const ViewDev* views, const uint32_t* scan_local,
+                       const uint2* trect, int ax, int ay, uint32_t pack_mask, int64_t n_slots,
+                       int32_t n_gauss, const ViewDev* views, const uint32_t* scan_local,
                        const uint32_t* block_sums, uint32_t capacity, uint32_t* inst_tile,
                        uint32_t* inst_val, hipStream_t s) {
   if (n_slots <= 0) return;
   const int nblocks = (int)((n_slots + kScanChunk - 1) / kScanChunk);
   const int n_views = (int)(n_slots / n_gauss);
-  hipLaunchKernelGGL(emit_kernel, dim3(nblocks), dim3(kScanBlock), 0, s, sorted_slots,
-                     rect_sorted, trect, n_slots, n_gauss, n_views, views, scan_local,
-                     block_sums, nblocks, capacity, inst_tile, inst_val);
+  const int extra = nblocks <= kInlineBlocks ? kEmitExtra : 0;
+  hipLaunchKernelGGL(emit_kernel, dim3(nblocks + extra), dim3(kScanBlock), 0, s, sorted_slots,
+                     rect_sorted, trect, ax, ay, pack_mask, n_slots, n_gauss, n_views, views,
+                     scan_local, block_sums, nblocks, capacity, inst_tile, inst_val);
 }
 
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t value, hipStream_t s) {
