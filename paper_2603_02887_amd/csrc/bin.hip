@@ -255,34 +255,47 @@ __global__ __launch_bounds__(kBThreads) void cell_scan_kernel(uint32_t* __restri
 }
 
 // Where each cell's pairs, segments (of 2^seg_shift pairs, the last one
-// shorter) and instances begin: start[d], d <= n_cells for the first two.
+// shorter) and instances begin: start[d], d <= n_cells for the first two.  (Every
+// cell in one round of loads and scans: 3,094 cells 6.1 us, in rounds of 1,024
+// cells 9.)
 __global__ __launch_bounds__(kStartThreads) void cell_starts_kernel(
     const uint32_t* __restrict__ totals, const uint32_t* __restrict__ weights, uint32_t n_cells,
     uint32_t seg_shift, uint32_t* __restrict__ pair0, uint32_t* __restrict__ seg0,
     uint32_t* __restrict__ inst0, const Counters* __restrict__ cnt) {
   constexpr int NW = kStartThreads / 64;
+  constexpr int PER = kMaxCells / kStartThreads;   // consecutive cells per thread: one round
+  static_assert(kMaxCells % kStartThreads == 0, "whole cells per thread");
   __shared__ uint32_t s_tmp[NW];
   if (cnt->fail) return;
-  uint32_t p = 0, g = 0, m = 0;
-  for (uint32_t b = 0; b < n_cells; b += kStartThreads) {
-    const uint32_t d = b + threadIdx.x;
-    const uint32_t v = d < n_cells ? totals[d] : 0u, w = d < n_cells ? weights[d] : 0u;
-    const uint32_t sg = (v + (1u << seg_shift) - 1u) >> seg_shift;
-    uint32_t tp, tg, tm;
-    const uint32_t ep = bin_block_scan<NW>(v, s_tmp, &tp), eg = bin_block_scan<NW>(sg, s_tmp, &tg);
-    const uint32_t em = bin_block_scan<NW>(w, s_tmp, &tm);
+  uint32_t v[PER], w[PER], p = 0, g = 0, m = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const uint32_t d = threadIdx.x * PER + q;
+    v[q] = d < n_cells ? totals[d] : 0u;
+    w[q] = d < n_cells ? weights[d] : 0u;
+    p += v[q];
+    g += (v[q] + (1u << seg_shift) - 1u) >> seg_shift;
+    m += w[q];
+  }
+  uint32_t tp, tg, tm;
+  p = bin_block_scan<NW>(p, s_tmp, &tp);
+  g = bin_block_scan<NW>(g, s_tmp, &tg);
+  m = bin_block_scan<NW>(m, s_tmp, &tm);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const uint32_t d = threadIdx.x * PER + q;
     if (d < n_cells) {
-      pair0[d] = p + ep;
-      seg0[d] = g + eg;
-      inst0[d] = m + em;
+      pair0[d] = p;
+      seg0[d] = g;
+      inst0[d] = m;
     }
-    p += tp;
-    g += tg;
-    m += tm;
+    p += v[q];
+    g += (v[q] + (1u << seg_shift) - 1u) >> seg_shift;
+    m += w[q];
   }
   if (threadIdx.x == 0) {
-    pair0[n_cells] = p;
-    seg0[n_cells] = g;
+    pair0[n_cells] = tp;
+    seg0[n_cells] = tg;
   }
 }
 
@@ -464,6 +477,28 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
   }
 }
 
+// The cells' first segments into LDS, eight loads of a thread in flight at a time (a
+// load after the other is most of the kernel's time where segments are few: 3,094
+// cells of 60 pairs, seg_count 7.6 -> 5.5 us, seg_emit 10.3 -> 9.2).
+__device__ __forceinline__ void load_starts(uint32_t* s_seg, const uint32_t* __restrict__ seg0,
+                                            uint32_t n_cells) {
+  constexpr int PER = 8;
+  if (n_cells < kBThreads) {
+    if (threadIdx.x <= n_cells) s_seg[threadIdx.x] = seg0[threadIdx.x];
+    return;
+  }
+  for (uint32_t d0 = 0; d0 <= n_cells; d0 += PER * kBThreads) {
+    uint32_t v[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) v[q] = seg0[min(d0 + q * kBThreads + threadIdx.x, n_cells)];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const uint32_t d = d0 + q * kBThreads + threadIdx.x;
+      if (d <= n_cells) s_seg[d] = v[q];
+    }
+  }
+}
+
 // the cell of segment sg (the last d with s_seg[d] <= sg; sg is below the total)
 __device__ __forceinline__ uint32_t cell_of_segment(const uint32_t* s_seg, uint32_t n_cells,
                                                     uint32_t sg) {
@@ -517,7 +552,7 @@ __global__ __launch_bounds__(kBThreads) void seg_count_kernel(
   constexpr int NT = 1 << (SX + SY);
   __shared__ uint32_t s_seg[kMaxCells + 1];
   if (cnt->fail) return;
-  for (uint32_t d = threadIdx.x; d <= n_cells; d += kBThreads) s_seg[d] = seg0[d];
+  load_starts(s_seg, seg0, n_cells);
   __syncthreads();
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t n_seg = s_seg[n_cells];
@@ -619,7 +654,7 @@ __global__ __launch_bounds__(kBThreads) void seg_emit_kernel(
   constexpr int NT = 1 << (SX + SY);
   __shared__ uint32_t s_seg[kMaxCells + 1];
   if (cnt->fail) return;
-  for (uint32_t d = threadIdx.x; d <= n_cells; d += kBThreads) s_seg[d] = seg0[d];
+  load_starts(s_seg, seg0, n_cells);
   __syncthreads();
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t n_seg = s_seg[n_cells];
