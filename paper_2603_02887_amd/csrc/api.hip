@@ -129,6 +129,7 @@ struct nxs_context {
   // instances of the context's last known render: a deferred render's tile
   // sort and ranges are launched for about this many (and loop beyond it)
   uint64_t m_hint = 0;
+  bool by_cell = false;   // the last render (begun) was binned in two levels
   int64_t last_bwd_slots = -1;   // slots of the last backward (inspection)
 };
 
@@ -424,10 +425,12 @@ nxs_status check_args(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera
   return NXS_OK;
 }
 
-// The forward of include/nxs.h, arguments already checked.
-nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* cams,
-                   int32_t n_views, const nxs_render_opts* opts, const nxs_image* out,
-                   const Checked& c, nxs_fwd_state** state_out, hipStream_t s) {
+// The forward of include/nxs.h, arguments already checked.  (cells: whether it may
+// be binned in two levels; ctx->by_cell says whether it was.)
+nxs_status forward_once(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* cams,
+                        int32_t n_views, const nxs_render_opts* opts, const nxs_image* out,
+                        const Checked& c, nxs_fwd_state** state_out, hipStream_t s, bool cells) {
+  ctx->by_cell = false;
   const int tw = c.tw, th = c.th, sched = c.sched;
   const int64_t total_tiles = c.total_tiles, S = c.S;
   HIP_TRY(hipSetDevice(ctx->device));
@@ -496,13 +499,13 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
   // passes, and loses (640x200, 520 tiles, 100k: 115 against 111); so it does for
   // many slots (four views of 600k, 484 against 425) and many instances a slot
   // (1024x128, 200k of 1.9M, 147 against 117), whose number is only known from
-  // an earlier render (not asked where memory is limited: a context then keeps
-  // to one way).
-  const bool in_lds = bins.n_cells > 0 && !tile_first && g->n > 0 && g->n <= kLocalMax;
-  const bool many = !ctx->noalloc && !ctx->ws_limit && expect_m > (double)kEmitMost &&
-                    expect_m > 2.5 * (double)S;
+  // an earlier render.
+  const bool many = expect_m > (double)kEmitMost && expect_m > 2.5 * (double)S;
   const bool few_tiles = total_tiles <= (1 << kMaxDigitBits) && S <= kEmitMost && !many;
-  const bool by_cell = bins.n_cells > 0 && (in_lds || !few_tiles);
+  const bool small_views = !tile_first && g->n > 0 && g->n <= kLocalMax;
+  const bool by_cell = cells && bins.n_cells > 0 && (small_views || !few_tiles);
+  const bool in_lds = by_cell && small_views;
+  ctx->by_cell = by_cell;
   const bool small = by_cell && bins.small;
   const uint32_t slot_mask = bins.pack ? kPackMask : ~0u;
   const int ax = bins.ax, ay = bins.ay;
@@ -849,6 +852,36 @@ nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* c
     *state_out = fs;
   }
   return NXS_OK;   // (the guard records `done` on the stream)
+}
+
+// Where memory is limited (the no-alloc scratch, a workspace limit) a render that
+// does not fit is taken once more without what the other way of binning left
+// behind, and one binned in two levels once more with its instances emitted: few
+// slots over many cells need less memory so.
+nxs_status forward(nxs_context* ctx, const nxs_gaussians* g, const nxs_camera* cams,
+                   int32_t n_views, const nxs_render_opts* opts, const nxs_image* out,
+                   const Checked& c, nxs_fwd_state** state_out, hipStream_t s) {
+  nxs_status st = forward_once(ctx, g, cams, n_views, opts, out, c, state_out, s, true);
+  const bool limited = ctx->noalloc || ctx->ws_limit;
+  if (st != NXS_ECAPACITY || !limited || ctx->last_m >= 0xFFFFFFFFll) return st;
+  auto give_back = [&]() {
+    const size_t had = ctx->ws_total;
+    if (ctx->noalloc) {   // (the whole region, which this call alone has used)
+      free_workspace(ctx, s);
+      ctx->al.region_used = 0;
+      return true;
+    }
+    for (DevBuf* b : {&ctx->trect, &ctx->rect_sorted, &ctx->counts, &ctx->nt_sorted,
+                      &ctx->scan_local, &ctx->block_sums, &ctx->cells, &ctx->segs, &ctx->vis})
+      drop(ctx, *b, s, true);
+    return ctx->ws_total < had;
+  };
+  const bool cells = ctx->by_cell;
+  if (!ctx->noalloc && give_back())
+    st = forward_once(ctx, g, cams, n_views, opts, out, c, state_out, s, true);
+  if (st != NXS_ECAPACITY || !cells) return st;
+  (void)give_back();
+  return forward_once(ctx, g, cams, n_views, opts, out, c, state_out, s, false);
 }
 
 }  // namespace
@@ -1462,6 +1495,8 @@ nxs_status nxs_inspect_projection(nxs_context* ctx, int32_t view, uint32_t* dept
   const int64_t n = ctx->last_n;
   if (capacity < n) return fail(ctx, NXS_EINVAL, "capacity below n");
   if (n == 0) return NXS_OK;
+  if (!ctx->depth_key.p || !ctx->trect.p)
+    return fail(ctx, NXS_EINVAL, "the last render did not complete");
   HIP_TRY(hipSetDevice(ctx->device));
   HIP_TRY(hipEventSynchronize(ctx->done));
   std::vector<uint2> rect(n);

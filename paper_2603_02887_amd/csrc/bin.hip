@@ -741,6 +741,9 @@ BinPlan plan_bins(const int32_t* tiles_x, const int32_t* tiles_y, int n_views, i
   p.chunk = large ? kMaxCellChunk : 1024;
   while (p.chunk > kMinChunk && (int64_t)n * n_views < kWantChunks * p.chunk) p.chunk /= 2;
   p.seg_shift = large ? 10 : (int64_t)n * n_views >= kMidFrom ? 8 : 6;
+  // (a row of a cell's tiles per segment: at most half a word a pair, so that the
+  // rows fit where the tile-sorted instances would lie)
+  p.seg_shift = std::max(p.seg_shift, (uint32_t)(p.sx + p.sy + 1));
   p.cpv = (uint32_t)((n + p.chunk - 1) / p.chunk);
   return p;
 }
