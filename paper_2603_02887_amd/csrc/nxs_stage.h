@@ -64,8 +64,8 @@ __device__ __forceinline__ StageBlock stage_shrink(const StageBlock& b, uint64_t
 // flight while earlier batches are composited: lane j takes list entry
 // base + j (if below end) and its slot (two batches ahead), then the slot's
 // record (one batch ahead).  Every lane reads (past the end: the list's last
-// entry again; an entry that does not cover the wave's block: the batch's first
-// record), so that no branch makes a read complete early.  Callers
+// entry again; an entry that does not cover the wave's block: slot 0's record,
+// whatever it holds), so that no branch makes a read complete early.  Callers
 // fetch only for a non-empty list (end > 0); for end = 0 the index would
 // still be 0, never end - 1 wrapped around.
 struct StageSlot {
@@ -93,7 +93,12 @@ __device__ __forceinline__ StageSlot stage_slot(const uint32_t* __restrict__ ins
 // composite of many small splats, and of a 16x16 tile's entries less than half
 // cover any one of its blocks: exponential composite of sixteen views of 3M
 // Gaussians 2,678 -> 1,647 us, linear one of eight 720p views 192 -> 165 us; the
-// 1080p frame's, whose splats' arithmetic costs as much, 132 us as before.)
+// 1080p frame's, whose splats' arithmetic costs as much, 132 us as before.  A
+// render whose time is a few very long lists loses up to 5 %, since each wave then
+// waits for its own records where its siblings' reads had brought them into L2: five
+// views of 124x499, 69k Gaussians, 481 -> 505 us.  Sharing slot 0's record rather
+// than the batch's first takes the readfirstlane out of that chain: two views of
+// 200x77, 2M, 927 -> 903.)
 __device__ __forceinline__ StageFetch stage_records(const StageSlot& s,
                                                     const float4* __restrict__ rec,
                                                     uint32_t slot_mask, int wid) {
@@ -101,8 +106,7 @@ __device__ __forceinline__ StageFetch stage_records(const StageSlot& s,
   const uint32_t blocks = (s.entry | (slot_mask == ~0u ? ~0u : 0u)) >> 28;
   f.valid = s.valid && ((blocks >> wid) & 1u);
   f.slot = s.entry & slot_mask;
-  const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)f.slot);
-  f.slot = f.valid ? f.slot : first;
+  f.slot = f.valid ? f.slot : 0u;
   const float4* r = rec + 3 * (size_t)f.slot;
   f.r0 = r[0];
   f.r1 = r[1];
