@@ -6,8 +6,8 @@
 Workload: 1,000,000 Gaussians drawn from 64 anisotropic clusters, SH degree 3,
 one 1920x1080 pinhole camera.  One step renders that frame once with each
 transmittance model (exponential, linear, quadratic sublinear, quadratic
-superlinear): the whole path (projection, depth sort, binning, tile sort,
-tile ranges, composite with its gather) runs for every render, with the
+superlinear): the whole path (projection, depth sort, binning with its tile
+ranges, composite with its gather) runs for every render, with the
 tile shape, composite schedule and LDS batch the library's autotuner picks
 for each model.  The scene is uploaded to HBM before the timed region.
 
@@ -102,13 +102,40 @@ def depth_sort_passes(scene, cam):
     return 3 if nbits <= 27 else 4
 
 
-def stage_roofline(m, scene, cam, conf, counts, od, stage_ms, thr_ms):
+# The library bins one view in two levels when it has more than 512 tiles and
+# cells of at most 8x8 tiles divide it into at most 512; its slots' rectangles
+# are one word where the view has at most 255 8x8 blocks either way.
+CELL_SHAPES = ((4, 4), (8, 4), (8, 8))
+CELLS_PER_VIEW = 512
+EMIT_TILES = 512
+WORD_RECT_BLOCKS = 255
+
+
+def cell_pairs(rects, tiles_x, tiles_y):
+    """(slot, cell) pairs of a view binned in two levels, from its slots' tile
+    rectangles (x0, x1, y0, y1 inclusive; x0 < 0: culled); None for a view
+    whose instances are emitted and sorted by tile."""
+    if tiles_x * tiles_y <= EMIT_TILES:
+        return None
+    for w, h in CELL_SHAPES:
+        if -(-tiles_x // w) * -(-tiles_y // h) <= CELLS_PER_VIEW:
+            r = np.asarray(rects, np.int64)
+            r = r[r[:, 0] >= 0]
+            return int(((r[:, 1] // w - r[:, 0] // w + 1)
+                        * (r[:, 3] // h - r[:, 2] // h + 1)).sum())
+    return None
+
+
+def stage_roofline(m, scene, cam, conf, counts, od, stage_ms, thr_ms, pairs=None):
     """T_roof = sum over stages of max(algorithmic bytes / 8 TB/s, lane-ops /
     39.3 T lane-ops/s), per stage and overall, against the stages measured
     alone and against one render's share of the throughput mode.  Algorithmic
     bytes are those this pipeline must move: S slots (one view), M tile
-    instances, T tiles, P pixels; the composite's lane-ops are 24 per
-    composited pair."""
+    instances, T tiles, P pixels and, binned in two levels, the (slot, cell)
+    pairs (None: every instance emitted and sorted by tile); the composite's
+    lane-ops are 24 per composited pair.  Two levels: "emit" is the dealing to
+    the cells, "tile_sort" the cells' lists expanded into the tiles' and
+    "ranges" the longest-first tile order."""
     M, T = counts
     S = scene.n
     P = cam.width * cam.height
@@ -121,6 +148,20 @@ def stage_roofline(m, scene, cam, conf, counts, od, stage_ms, thr_ms):
          "tile_sort": 16 * M * tpass,
          "ranges": 4 * M + 8 * T,
          "composite": 52 * M + 20 * P}                    # slot index + record per entry; image
+    if pairs is not None:
+        tw, th = conf["tile"]
+        blocks = max(-(-cam.width // tw) * (tw // 8), -(-cam.height // th) * (th // 8))
+        rect = 4 if blocks <= WORD_RECT_BLOCKS else 8
+        order = 4 * S if conf["sort_order"] != "tile_first" else 0
+        b["project"] = (56 + 12 * K) * scene.n + (52 + rect) * S
+        b["depth_sort"] = 16 * S * dpass + 2 * rect * S   # the rectangles gathered in order
+        # rectangles counted, then read again with the slots; pairs of a slot and
+        # 2 bytes of rectangle
+        b["emit"] = 2 * rect * S + order + 6 * pairs
+        # the pairs' rectangles, then the pairs; the lists and their ranges
+        b["tile_sort"] = 8 * pairs + 4 * M + 8 * T
+        b["ranges"] = 12 * T if conf.get("schedule") in ("queue", "persistent") else 0
+        tpass = 0
     if conf["sort_order"] == "tile_first":                # per-tile depth sort in "ranges"
         b["ranges"] += (16 * dpass + 4) * M
         b["depth_sort"] = 0
@@ -675,6 +716,13 @@ def main():
             stages[m].append(R.stage_times())
             counts[m] = R.counts()   # (instances, tiles) of this model's configuration
     R.set_timing(False)
+    pairs = {}   # (slot, cell) pairs of each tile shape
+    for m in range(4):
+        tw, th = cfg[m]["tile"]
+        if (tw, th) not in pairs:
+            render(m, deferred=False)
+            pairs[tw, th] = cell_pairs(R.projection(0, scene.n)[1], -(-cam.width // tw),
+                                       -(-cam.height // th))
 
     per_model = {}
     stage_mean = {}
@@ -723,7 +771,8 @@ def main():
     renders = 4 * args.steps
     value = W * H * renders / total / 1e6
     stage_roof = {MODELS[m]: stage_roofline(m, scene, cam, cfg[m], counts[m], od_sum[m],
-                                            stage_mean[m], total / renders)
+                                            stage_mean[m], total / renders,
+                                            pairs[tuple(cfg[m]["tile"])])
                   for m in range(4)}
     exp_ms = per_model["exponential"]["ms_per_render"]
     for name in MODELS[1:]:
