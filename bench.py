@@ -70,11 +70,11 @@ HBM_PEAK_GBS = 8000.0
 # size (profiles/forward_hbm_traffic_scene1m_1080p.md).  They describe the
 # kernel sources with this digest and are reported as null once those change.
 TRAFFIC_SOURCES = ("composite.hip", "nxs_ops.h", "nxs_stage.h", "nxs_internal.h")
-TRAFFIC = {"digest": "c20a0206352d4c4321e69bec35929240f80d2fdcfc2f1abbf861f0214ba677ec",
+TRAFFIC = {"digest": "08900c8cf26526c0f865996173fbdc450cde7c687f72ee515c45c179c1de716e",
            "tile": "16x16",
            "bytes": {
-               "queue": {0: 295754059, 1: 165880810, 2: 184941911, 3: 160143950},
-               "tiles": {0: 215889894, 1: 123659493, 2: 136976199, 3: 119775502}}}
+               "queue": {0: 295867001, 1: 166227157, 2: 184673603, 3: 160087480},
+               "tiles": {0: 215398057, 1: 123471836, 2: 136732106, 3: 119547172}}}
 
 
 def measured_traffic(model, tile, schedule):

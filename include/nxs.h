@@ -140,9 +140,11 @@ typedef struct {
   float param;            /* operator parameter of models 4..7 (c, gamma or v) */
   int32_t flags;          /* NXS_FLAG_* */
   int32_t schedule;       /* nxs_schedule of the composite; 0 -> NXS_SCHED_QUEUE */
-  float instance_hint;    /* deferred renders: the tile instances the caller
-                             expects (0 -> the context's last count); sizes the
-                             binning's launches, never the result */
+  float instance_hint;    /* the tile instances the caller expects (0 -> the
+                             context's last count): a deferred render sizes its
+                             binning's launches for them, and a render of few
+                             tiles chooses its way of binning by them; never
+                             the result */
   int32_t sort_order;     /* nxs_sort_order; 0 -> NXS_SORT_AUTO */
 } nxs_render_opts;
 
@@ -153,9 +155,8 @@ typedef struct {
  *   TILE_FIRST   bin the Gaussians stably by tile in their own order, then sort
  *                each tile's list by depth in on-chip memory (a list longer
  *                than 4,096 entries is sorted through device memory)
- *   AUTO         TILE_FIRST when the expected instances per tile (the
- *                caller's instance_hint, else the context's last count) are
- *                at most 1,024 on average, else DEPTH_FIRST */
+ *   AUTO         DEPTH_FIRST, the faster one in every render measured
+ *                (nxs_autotune measures both) */
 typedef enum {
   NXS_SORT_AUTO = 0,
   NXS_SORT_DEPTH_FIRST = 1,

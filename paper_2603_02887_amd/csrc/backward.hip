@@ -57,14 +57,15 @@ constexpr int kRor4 = 0x124;                               // row_ror:4
 // bound by VALU issue (88% busy): this takes about 18 instructions a splat,
 // where forming nine products in every lane and adding them over lane quads
 // took 32 and nine LDS writes (8 views of 720p, 500k splats: 910 -> 770 us;
-// 1080p, 1M, quadratic: 132 -> 115 us).  Eight splats a flush need fewer
-// instructions but 4 KB more LDS a work-group, and lose to it (1013 us at five
-// waves a SIMD).  The table is sized so that eight work-groups fit a CU's LDS.
+// 1080p, 1M, quadratic: 132 -> 115 us).  Six work-groups of four waves fit a CU by
+// their registers (77 to 80), eight by 20 KB of LDS; with eight splats a flush, 2 KB
+// more a wave and 28 KB a work-group, five fit, and that loses although it needs
+// fewer instructions (1013 us).
 constexpr int kRedSplats = 4;
 constexpr int kRedF4 = 2 * kRedSplats * 64 / 4;  // float4 per wave
 
 // (six waves a SIMD: left to itself the compiler takes 82 registers for the
-// quadratic operators, two more than six waves have)
+// quadratic operators, two more than six waves leave each)
 template <int MODEL, int TW, int TH>
 __global__ __launch_bounds__(TW* TH, 6) void composite_bwd_kernel(
     const ViewDev* __restrict__ views, int n_views, const uint2* __restrict__ ranges,

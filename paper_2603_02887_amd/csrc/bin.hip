@@ -24,11 +24,11 @@
 // never sorted: the pairs that are moved by cell number one to three per slot.
 // Emitting every instance and sorting all of them by tile (two radix passes of
 // 8-byte pairs, then the ranges) moved each one five times: 845 us for the 62M
-// instances of eight 720p views of 500k Gaussians, 274 us here; 78 against
-// 62 us for the 2.69M of the 1080p frame of 1M; 1,650 against 1,170 us for the
+// instances of eight 720p views of 500k Gaussians, 257 us here; 78 against
+// 60 us for the 2.69M of the 1080p frame of 1M; 1,650 against 1,150 us for the
 // 99M of sixteen views of 3M.
 // Every kernel is bound by the latency of its steps at a few million pairs and
-// by VALU beyond (seg_emit: 113 us of the 274, 2.2 TB/s of list writes).
+// by VALU beyond (seg_emit: 102 us of the 257, 2.4 TB/s of list writes).
 // Each view is binned on its own (its slots are one part of the depth sort),
 // so that a view's cells fit the tables of the scatter.
 // The tiles' lists lie cell by cell; `ranges` says where.
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kBThreads) void cell_scatter_kernel(
   }
   const int64_t end = ck.end;
   for (int64_t base = ck.first; base < end; base += kSub) {
-    // two consecutive slots per thread
+    // kSubPerT consecutive slots per thread
     const int k0 = kSubPerT * t;
     uint32_t a[kSubPerT], e[kSubPerT], total;
     {

@@ -1,5 +1,5 @@
 // Depth sort of small views in LDS: a view of at most kLocalMax slots is one
-// work-group's, in one kernel instead of the radix sort's nine or twelve.
+// work-group's, in one kernel instead of the radix sort's nine or twelve launches.
 //
 // The keys, relative to their least, are dealt by LDS atomics to 2,048 bins of
 // equal steps, in no particular order within a bin, and each key then takes its
@@ -8,10 +8,10 @@
 // quadratic: such a view is sorted by stable passes of up to 8 bits, in LDS too
 // (8,192 slots on two planes, a 128x128 render: 89 us, with passes through memory
 // 125, with the radix sort 87 to 92; 4,096: 82, 94, 87 to 92).
-// Bound by the latency of its dozen steps: 13.5 us for 4,096 slots, where the
-// radix sort's nine launches took 35 (a 128x128 render of 4,096 Gaussians
-// 112 -> 80 us).  (Larger views dealt to 512 buckets by a sampled table first, and
-// each bucket sorted so, measured no faster than the radix sort: 66 against
+// Bound by the latency of its dozen steps: 12.2 us for 4,096 slots, where the
+// radix sort's twelve launches took 45 (a 128x128 render of 4,096 Gaussians
+// 111 -> 84 us).  (Larger views dealt to 512 parts by a sampled table first, and
+// each part sorted so, measured no faster than the radix sort: 66 against
 // 68 us for 1M slots, 124 against 132 us for 4M.)
 #include "nxs_internal.h"
 
@@ -249,7 +249,7 @@ __device__ uint32_t sort_lds(const uint32_t* __restrict__ keys, int m, SortLds& 
   return seen;
 }
 
-// Rectangles of either kind (ProjDev): one moved, and an array's part from i on.
+// A rectangle of either kind (ProjDev), moved.
 __device__ __forceinline__ void copy_rect(uint2* __restrict__ to, size_t j,
                                           const uint2* __restrict__ from, uint32_t i, bool small) {
   if (small)

@@ -370,9 +370,6 @@ void launch_tile_depth_sort(const uint2* ranges, int64_t n_tiles, const uint32_t
                             const Counters* counters, uint32_t slot_mask, uint32_t* list,
                             uint32_t* temp, hipStream_t s);
 
-
-
-
 // Tile ranges: ranges[tile] = [first, end) of the tile's entries in the
 // tile-sorted instance list (tiles without instances keep what the caller
 // filled in, normally [0, 0)).

@@ -1,5 +1,7 @@
-// Binning: the scan + emission of tile instances and the tile ranges (the
-// radix sort itself is in radix.hip; the gather of records into sorted order
+// Binning of the renders that emit every tile instance and sort them by tile:
+// those of few tiles, and those of more cells or views than the binning in two
+// levels (bin.hip) takes.  The scan + emission of the instances and the tile ranges
+// (the radix sort itself is in radix.hip; the gather of records into sorted order
 // happens batch by batch inside the composite).
 //
 // Front-to-back order inside each tile (Sec. 3: splats sorted by depth) is
@@ -18,7 +20,6 @@
 namespace nxs {
 
 namespace {
-
 
 // Block-wide exclusive scan of one value per thread (256 threads).
 template <int NW = 4>   // waves in the work-group
