@@ -32,9 +32,6 @@ namespace nxs {
 
 namespace {
 
-constexpr float kL2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;   // 1 / log2(e)
-
 // x + the y of another lane of the row of 16 (CTRL; 0 where there is none).
 // (no contraction: an add of the moved value folds into one DPP add, which a
 // product of the caller fused into an FMA with it would prevent)
